@@ -65,6 +65,21 @@ regenvc_status regenvc_linear_fwd(const void *a, int64_t lda, const void *w, con
                                   const float *gate, void *out, int64_t ldo, int32_t M, int32_t N,
                                   int32_t K, int32_t epilogue, void *stream);
 
+/* The same with a workspace (256-byte aligned device memory, or NULL and 0)
+   for the split-K form: where the output has too few tiles for the chip, K
+   is cut into ranges whose f32 partial sums go to the workspace and a second
+   kernel adds them, in order, with the epilogue.  A workspace smaller than
+   regenvc_linear_workspace gives fewer ranges; without one the call is
+   regenvc_linear_fwd.  Neither call allocates. */
+regenvc_status regenvc_linear_fwd_ws(const void *a, int64_t lda, const void *w, const void *bias, const float *gate,
+                                     void *out, int64_t ldo, int32_t M, int32_t N, int32_t K, int32_t epilogue,
+                                     void *workspace, int64_t workspace_bytes, void *stream);
+
+/* Workspace bytes of the split-K form on n_cu compute units (0: the shape is
+   not split).  Host-only. */
+regenvc_status regenvc_linear_workspace(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t n_cu,
+                                        int64_t *bytes);
+
 /* Layer normalization of the f32 rows of x [rows, C] (row stride ldx) into
    bf16 y (row stride ldy): LN(x) (1 + scale) + shift with f32 shift, scale
    [C] (the adaLN-modulated form; w, b NULL), or LN(x) w + b with bf16 w, b

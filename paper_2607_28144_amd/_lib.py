@@ -75,6 +75,10 @@ _SIGNATURES = {
     "regenvc_attn_set_workspace": [ctypes.c_void_p, ctypes.c_int64],
     "regenvc_linear_fwd": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                            ctypes.c_void_p, ctypes.c_int64, _i32, _i32, _i32, _i32, ctypes.c_void_p],
+    "regenvc_linear_fwd_ws": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
+                              ctypes.c_void_p, ctypes.c_int64, _i32, _i32, _i32, _i32, ctypes.c_void_p,
+                              ctypes.c_int64, ctypes.c_void_p],
+    "regenvc_linear_workspace": [_i32, _i32, _i32, _i32, _i32, ctypes.POINTER(ctypes.c_int64)],
     "regenvc_layer_norm_fwd": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p,
                                ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, _i32, _i32, ctypes.c_float,
                                ctypes.c_void_p],

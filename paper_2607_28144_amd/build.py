@@ -6,6 +6,8 @@ called.  Packed-fp32 VALU instructions are switched off for all device code.
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 REPO_DIR = os.path.dirname(PKG_DIR)
@@ -15,6 +17,10 @@ LIB_PATH = os.path.join(PKG_DIR, LIB_NAME)
 SOURCES = ["api.cpp", "attn_fwd.hip", "lse_merge.hip", "norm_rope.hip", "dit_api.cpp", "dit.hip", "vae_api.cpp",
            "vae.hip"]
 ARCH = "gfx950"
+# MFMA results in VGPRs: the score tiles feed VALU softmax code directly, and
+# read-only operands may then live in AGPRs.  Not for the tile kernels of the
+# linear layers, whose accumulators fill the AGPRs.
+VGPR_FORM = {"attn_fwd.hip"}
 
 
 def hipcc() -> str:
@@ -25,31 +31,37 @@ def hipcc() -> str:
 def build(verbose: bool = False) -> str:
     """Compile the shared library; returns its path.  Raises on failure."""
     out_tmp = LIB_PATH + ".tmp"
-    cmd = [
-        hipcc(),
+    flags = [
         f"--offload-arch={ARCH}",
         "-O3",
         "-std=c++17",
         "-fPIC",
-        "-shared",
         "-Wall",
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        # MFMA results in VGPRs: the score tiles feed VALU softmax code directly,
-        # and read-only operands may then live in AGPRs
-        "-mllvm", "-amdgpu-mfma-vgpr-form",
         "-I", os.path.join(REPO_DIR, "include"),
         "-I", CSRC,
-        "-o", out_tmp,
-    ] + [os.path.join(CSRC, s) for s in SOURCES]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    # the host pass does not know the packed-fp32 feature: that warning is harmless
-    msgs = [ln for ln in (res.stdout + res.stderr).splitlines() if "packed-fp32-ops" not in ln]
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
-    if verbose and msgs:
-        print("\n".join(msgs), flush=True)
+    ]
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        # the host pass does not know the packed-fp32 feature: that warning is harmless
+        msgs = [ln for ln in (res.stdout + res.stderr).splitlines() if "packed-fp32-ops" not in ln]
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
+        if verbose and msgs:
+            print("\n".join(msgs), flush=True)
+
+    def compile_one(name, obj):
+        extra = ["-mllvm", "-amdgpu-mfma-vgpr-form"] if name in VGPR_FORM else []
+        run([hipcc()] + flags + extra + ["-c", "-o", obj, os.path.join(CSRC, name)])
+
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        with ThreadPoolExecutor(max_workers=4) as pool:
+            list(pool.map(compile_one, SOURCES, objs))
+        run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", out_tmp] + objs)
     os.replace(out_tmp, LIB_PATH)
     return LIB_PATH
 

@@ -5,13 +5,16 @@
 // modulation vectors.
 //
 // Linear layer y = a W^T, a [M, K] and W [N, K] both K-contiguous (the weight
-// layout of a linear layer): the shared bf16 MFMA tile kernel (gemm_tile.hpp)
-// with dense A rows and BM x 256 tiles (waves 2 x 4, each (BM/2) x 64), BM
-// 256 or 288 by how the tiles fill whole rounds of the compute units.
+// layout of a linear layer): the bf16 MFMA tile kernels of gemm_tile.hpp with
+// dense rows, four waves per tile of 64 x 128 to 256 x 256 or eight per
+// 288 x 256, K split over workgroups where the tiles are few (linear_plan).
 #include "dit_kernels.hpp"
 
 #include <math.h>
 
+#include <algorithm>
+
+#include "attn_kernels.hpp"
 #include "gemm_tile.hpp"
 
 namespace regenvc {
@@ -23,7 +26,7 @@ using tile::kThreads;
 typedef tile::bf16x8 bf16x8;
 typedef tile::f32x4 f32x4;
 
-constexpr int kBN = 256;   // output channels per linear tile (four waves of 64 across)
+constexpr int kBN = 256;   // output channels per eight-wave tile (four waves of 64 across)
 
 // Dense A rows: row m of a [M, K] bf16 matrix with row stride lda.
 struct DenseA {
@@ -34,7 +37,7 @@ struct DenseA {
     __device__ const uint16_t *src(Row r, int kt) const { return r + kt * kBK; }
 };
 
-// Linear layer, one BM x 256 tile per workgroup.
+// Linear layer, one BM x 256 tile per workgroup of eight waves.
 template <int BM, int EPI>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void linear_kernel(LinearArgs a, int tiles_n, int n_tiles)
@@ -44,6 +47,83 @@ void linear_kernel(LinearArgs a, int tiles_n, int n_tiles)
     const tile::Out o{static_cast<const uint16_t *>(a.w), static_cast<const uint16_t *>(a.bias), a.gate, a.out,
                       a.ldo, a.M, a.N, a.K};
     tile::tile_body<BM, 4, EPI>(src, o, tiles_n, n_tiles, smem);
+}
+
+// Four-wave tiles of a linear layer.
+typedef tile::Shape4<8, 8, 3, 1> Tile256x256;
+typedef tile::Shape4<5, 8, 3, 1> Tile160x256;
+typedef tile::Shape4<6, 6, 3, 1> Tile192x192;
+typedef tile::Shape4<4, 4, 3, 2> Tile128x128;
+typedef tile::Shape4<2, 4, 2, 3> Tile64x128;
+
+// Row strides from which the offsets within a tile (255 rows) may leave 32 bits.
+constexpr int64_t kWideStride = 1 << 22;
+
+// Linear layer, one tile of shape S per workgroup of four waves.  EPI ==
+// kPartial: K range blockIdx.x / n_tiles of `splits`, f32 sums to its
+// [M][N] plane of the workspace.
+template <class S, int EPI, bool WIDE>
+__global__ __launch_bounds__(tile::kThreads4) __attribute__((amdgpu_waves_per_eu(S::WPE, S::WPE)))
+void linear4_kernel(LinearArgs a, int tiles_n, int n_tiles, int splits)
+{
+    __shared__ __attribute__((aligned(1024))) char smem[S::LDS];
+    constexpr bool PART = EPI == tile::kPartial;
+    const int sp = PART ? (int)blockIdx.x / n_tiles : 0;
+    int tm, tn;
+    tile::tile_of((int)blockIdx.x - sp * n_tiles, tiles_n, n_tiles, tm, tn);
+    const int m0 = tm * S::BM, n0 = tn * S::BN;
+    const int nk = a.K / kBK;
+    const int k0 = PART ? (int)((int64_t)sp * nk / splits) : 0;
+    const int k1 = PART ? (int)((int64_t)(sp + 1) * nk / splits) : nk;
+    const tile::Dense<WIDE> as{static_cast<const uint16_t *>(a.a), a.lda, a.M, m0};
+    const tile::Dense<WIDE> ws{static_cast<const uint16_t *>(a.w), a.K, a.N, n0};
+    f32x4 acc[S::NB][S::MB];
+    if (k1 > k0) {
+        tile::mma4<S>(as, ws, k0, k1, smem, acc);
+    } else {
+#pragma unroll
+        for (int nb = 0; nb < S::NB; ++nb)
+#pragma unroll
+            for (int mb = 0; mb < S::MB; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const tile::Out o{nullptr, static_cast<const uint16_t *>(a.bias), a.gate, PART ? a.ws : a.out,
+                      PART ? (int64_t)a.N : a.ldo, a.M, a.N, a.K, splits};
+    tile::store4<S, EPI>(o, m0, n0, sp, smem, acc);
+}
+
+// Sum of the split-K partials and the epilogue: one thread per 8 channels of
+// one row.
+template <int EPI>
+__global__ __launch_bounds__(256) void linear_reduce_kernel(LinearArgs a, int splits)
+{
+    const int cg = a.N / 8;
+    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gid >= (int64_t)a.M * cg) return;
+    const int64_t m = gid / cg;
+    const int n = (int)(gid - m * cg) * 8;
+    const float *p = a.ws + m * a.N + n;
+    const int64_t plane = (int64_t)a.M * a.N;
+    f32x4 s[2] = {*reinterpret_cast<const f32x4 *>(p), *reinterpret_cast<const f32x4 *>(p + 4)};
+    for (int k = 1; k < splits; ++k) {
+        s[0] += *reinterpret_cast<const f32x4 *>(p + k * plane);
+        s[1] += *reinterpret_cast<const f32x4 *>(p + k * plane + 4);
+    }
+    s[0] += tile::load_bias4(static_cast<const uint16_t *>(a.bias), n);
+    s[1] += tile::load_bias4(static_cast<const uint16_t *>(a.bias), n + 4);
+    if constexpr (EPI == kEpiGatedRes) {
+        f32x4 *q = reinterpret_cast<f32x4 *>(static_cast<float *>(a.out) + m * a.ldo + n);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const f32x4 gv = a.gate != nullptr ? *reinterpret_cast<const f32x4 *>(a.gate + n + 4 * h)
+                                               : f32x4{1.f, 1.f, 1.f, 1.f};
+            q[h] = q[h] + gv * s[h];
+        }
+    } else {
+        bf16x8 o;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] = (__bf16)tile::activate<EPI>(s[i / 4][i % 4]);
+        *reinterpret_cast<bf16x8 *>(static_cast<uint16_t *>(a.out) + m * a.ldo + n) = o;
+    }
 }
 
 // ---------------------------------------------------------------- row norms
@@ -234,35 +314,120 @@ hipError_t launch_linear_bm(const LinearArgs &a, hipStream_t stream)
     return hipErrorInvalidValue;
 }
 
-int cu_count_here()
+template <class S, int EPI, bool WIDE>
+hipError_t launch_linear4_t(const LinearArgs &a, int splits, hipStream_t stream)
 {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 256;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
-    return n;
+    const int tiles_n = tile::tiles_along(a.N, S::BN), n_tiles = tile::tiles_along(a.M, S::BM) * tiles_n;
+    hipLaunchKernelGGL((linear4_kernel<S, EPI, WIDE>), dim3((unsigned)n_tiles * (unsigned)splits),
+                       dim3(tile::kThreads4), 0, stream, a, tiles_n, n_tiles, splits);
+    return hipGetLastError();
+}
+
+template <int EPI>
+hipError_t launch_reduce_t(const LinearArgs &a, int splits, hipStream_t stream)
+{
+    const int64_t n = (int64_t)a.M * (a.N / 8);
+    hipLaunchKernelGGL(linear_reduce_kernel<EPI>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a, splits);
+    return hipGetLastError();
+}
+
+template <class S, bool WIDE = false>
+hipError_t launch_linear4(const LinearArgs &a, int splits, hipStream_t stream)
+{
+    if constexpr (!WIDE) {
+        if (splits > 1) {
+            const hipError_t e = launch_linear4_t<S, tile::kPartial, false>(a, splits, stream);
+            if (e != hipSuccess) return e;
+            switch (a.epi) {
+            case kEpiBias: return launch_reduce_t<kEpiBias>(a, splits, stream);
+            case kEpiBiasGelu: return launch_reduce_t<kEpiBiasGelu>(a, splits, stream);
+            case kEpiGatedRes: return launch_reduce_t<kEpiGatedRes>(a, splits, stream);
+            }
+            return hipErrorInvalidValue;
+        }
+    }
+    switch (a.epi) {
+    case kEpiBias: return launch_linear4_t<S, kEpiBias, WIDE>(a, 1, stream);
+    case kEpiBiasGelu: return launch_linear4_t<S, kEpiBiasGelu, WIDE>(a, 1, stream);
+    case kEpiGatedRes: return launch_linear4_t<S, kEpiGatedRes, WIDE>(a, 1, stream);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-// Rounds of tiles over the CUs, each tile costing its rows: the 288-row tile
-// wins when the 256-row tiling spills a few tiles into an extra round (at
-// M = 10920 rows, 43 row blocks of 256 x 6 channel blocks = 258 tiles on 256
-// CUs; 38 blocks of 288 give 228 tiles, one round).
-int linear_tile_rows(int M, int N, int n_cu)
+// The tile and K split with the smallest estimated time.  A launch is whole
+// rounds of n_cu workgroups and one last, partly filled round; a workgroup
+// costs a fixed time (launch, first copies, epilogue) and a time per 64-deep
+// K step, measured on launches of at most one round (in us; 300 x 1536 x 1536
+// to 2000 x 1536 x 8960); full rounds run slower by `load`, at the clock that
+// the power limit leaves.  A split adds the second kernel: its launch, and the
+// partials written, read and reduced at memory speed.  Over 14 row counts
+// from 64 to 10920 of the block's five layers the choice is on average 1.2 %
+// slower than the best of all tiles and splits.  Measured, 256 x 256 by eight
+// waves before: 1365 x 1536 x 8960 203 -> 49 us (192 x 192 in four ranges),
+// 1560 x 4608 x 1536 39.7 -> 25.0 us (128 x 128), 10920 x 8960 x 1536 with
+// GELU 291 -> 270 us (256 x 256 by four waves); 10920 x 4608 and 10920 x 1536
+// stay with 288 x 256 by eight waves (138 and 46.7 us; the best other tile
+// 143 and 50.2: 228 tiles of 288 rows are one round where 43 row blocks of
+// 256 need 258 tiles).
+LinearPlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes)
 {
-    const int tn = (N + kBN - 1) / kBN;
-    auto cost = [&](int bm) {
-        const int64_t tiles = (int64_t)((M + bm - 1) / bm) * tn;
-        return (double)((tiles + n_cu - 1) / n_cu) * bm;
+    struct Cost {
+        int32_t tile, bm, bn;
+        float step, fixed[3], load;  // fixed: by epilogue
+        bool splits;
     };
-    return cost(288) < cost(256) ? 288 : 256;
+    static const Cost kCosts[] = {
+        {kTile256x256, 256, 256, 0.99f, {8.3f, 13.f, 20.f}, 1.32f, true},
+        {kTile160x256, 160, 256, 0.668f, {6.2f, 9.f, 14.f}, 1.32f, true},
+        {kTile192x192, 192, 192, 0.645f, {5.8f, 8.2f, 13.2f}, 1.32f, true},
+        {kTile128x128, 128, 128, 0.448f, {1.0f, 2.3f, 4.0f}, 1.02f, true},
+        {kTile64x128, 64, 128, 0.43f, {1.0f, 2.0f, 2.8f}, 1.02f, true},
+        {kTile288x256, 288, 256, 1.30f, {5.f, 9.f, 9.f}, 1.32f, false},
+    };
+    const int nk = K / kBK;
+    const int64_t plane = (int64_t)M * N * (int64_t)sizeof(float);
+    LinearPlan best{kTile288x256, 1};
+    double best_t = INFINITY;
+    for (const Cost &c : kCosts) {
+        const int64_t tiles = ((int64_t)M + c.bm - 1) / c.bm * (((int64_t)N + c.bn - 1) / c.bn);
+        const int max_splits = c.splits ? std::min(8, nk / 8) : 1;
+        for (int s = 1; s <= std::max(1, max_splits); ++s) {
+            if (s > 1 && (s * plane > ws_bytes || tiles * s > 2 * n_cu)) break;
+            if (tiles > 0x7fffffff / 8) break;
+            const double one = c.fixed[s > 1 ? (int)kEpiBias : epi] + (double)((nk + s - 1) / s) * c.step;
+            const int64_t full = tiles * s / n_cu, rest = tiles * s % n_cu;
+            double t = full * one * c.load;
+            if (rest > 0) t += one * (1.0 + (c.load - 1.0) * (double)rest / n_cu);
+            if (s > 1) t += 8.5 + ((double)plane * 2 * s + (double)M * N * (epi == kEpiGatedRes ? 8 : 2)) / 5.0e6;
+            if (t < best_t) best_t = t, best = LinearPlan{c.tile, s};
+        }
+    }
+    return best;
+}
+
+size_t linear_workspace_bytes(int M, int N, int K, int epi, int n_cu)
+{
+    if (M == 0 || N == 0 || K == 0) return 0;
+    const LinearPlan p = linear_plan(M, N, K, epi, n_cu, INT64_MAX);
+    return p.splits > 1 ? (size_t)p.splits * M * N * sizeof(float) : 0;
 }
 
 hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
 {
     if (a.M == 0 || a.N == 0) return hipSuccess;
-    return linear_tile_rows(a.M, a.N, cu_count_here()) == 288 ? launch_linear_bm<288>(a, stream)
-                                                               : launch_linear_bm<256>(a, stream);
+    if (a.K == 0 || a.lda >= kWideStride || a.K >= kWideStride) return launch_linear4<Tile128x128, true>(a, 1, stream);
+    const LinearPlan p = linear_plan(a.M, a.N, a.K, a.epi, device_cu_count(), a.ws != nullptr ? a.ws_bytes : 0);
+    switch (p.tile) {
+    case kTile256x256: return launch_linear4<Tile256x256>(a, p.splits, stream);
+    case kTile160x256: return launch_linear4<Tile160x256>(a, p.splits, stream);
+    case kTile192x192: return launch_linear4<Tile192x192>(a, p.splits, stream);
+    case kTile128x128: return launch_linear4<Tile128x128>(a, p.splits, stream);
+    case kTile64x128: return launch_linear4<Tile64x128>(a, p.splits, stream);
+    case kTile288x256: return launch_linear_bm<288>(a, stream);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_layer_norm(const LayerNormArgs &a, hipStream_t stream)

@@ -83,6 +83,15 @@ BlockLayout block_layout(int32_t S, int32_t S_ctx, int32_t C, int32_t heads, int
     if (regenvc::plan_attn(1, heads, S, S, D, n_cu, &p1)) need = (int64_t)regenvc::workspace_bytes(p1, D);
     if (regenvc::plan_attn(1, heads, S, S_ctx, D, n_cu, &p2))
         need = std::max(need, (int64_t)regenvc::workspace_bytes(p2, D));
+    // the split-K partials of a linear layer use the same scratch: the block's kernels run one after another
+    auto linear = [&](int N, int K, int epi) {
+        need = std::max(need, (int64_t)regenvc::linear_workspace_bytes(S, N, K, epi, n_cu));
+    };
+    linear(3 * C, C, regenvc::kEpiBias);
+    linear(C, C, regenvc::kEpiBias);
+    linear(C, C, regenvc::kEpiGatedRes);
+    linear(F, C, regenvc::kEpiBiasGelu);
+    linear(C, F, regenvc::kEpiGatedRes);
     L.total = L.scr + align256(need);
     return L;
 }
@@ -99,6 +108,33 @@ regenvc_status check_block_shape(const char *fn, int32_t S, int32_t S_ctx, int32
     return REGENVC_OK;
 }
 
+regenvc_status run_linear(const char *fn, const void *a, int64_t lda, const void *w, const void *bias,
+                          const float *gate, void *out, int64_t ldo, int32_t M, int32_t N, int32_t K, int32_t epilogue,
+                          void *ws, int64_t ws_bytes, void *stream)
+{
+    regenvc_status st = check_linear(fn, a, lda, w, bias, gate, out, ldo, M, N, K, epilogue);
+    if (st != REGENVC_OK) return st;
+    if (ws_bytes < 0) return failf(REGENVC_ERR_INVALID_ARG, "%s: workspace_bytes < 0", fn);
+    if (M == 0 || N == 0) {
+        regenvc::abi::clear_error();
+        return REGENVC_OK;
+    }
+    if (ws != nullptr) {
+        if (!aligned(ws, 256)) return failf(REGENVC_ERR_UNSUPPORTED, "%s: workspace must be 256-byte aligned", fn);
+        const auto rw = range_of(ws, ws_bytes);
+        const int esz = epilogue == REGENVC_EPI_GATED_RESIDUAL ? 4 : 2;
+        if (overlaps(rw, range_of(out, ((int64_t)(M - 1) * ldo + N) * esz)) ||
+            overlaps(rw, range_of(a, ((int64_t)(M - 1) * lda + K) * 2)) ||
+            overlaps(rw, range_of(w, (int64_t)N * K * 2)) || (bias && overlaps(rw, range_of(bias, (int64_t)N * 2))) ||
+            (gate && overlaps(rw, range_of(gate, (int64_t)N * 4))))
+            return failf(REGENVC_ERR_INVALID_ARG, "%s: workspace overlaps another argument", fn);
+    }
+    if ((st = regenvc::abi::device_ok()) != REGENVC_OK) return st;
+    const regenvc::LinearArgs la{a, w, bias, gate, out, lda, ldo, M, N, K, epilogue, static_cast<float *>(ws),
+                                 ws != nullptr ? ws_bytes : 0};
+    return regenvc::abi::launch_status(regenvc::launch_linear(la, static_cast<hipStream_t>(stream)), fn);
+}
+
 }  // namespace
 
 extern "C" {
@@ -107,16 +143,31 @@ regenvc_status regenvc_linear_fwd(const void *a, int64_t lda, const void *w, con
                                   void *out, int64_t ldo, int32_t M, int32_t N, int32_t K, int32_t epilogue,
                                   void *stream)
 {
-    const char *fn = "regenvc_linear_fwd";
-    regenvc_status st = check_linear(fn, a, lda, w, bias, gate, out, ldo, M, N, K, epilogue);
-    if (st != REGENVC_OK) return st;
-    if (M == 0 || N == 0) {
-        regenvc::abi::clear_error();
-        return REGENVC_OK;
-    }
-    if ((st = regenvc::abi::device_ok()) != REGENVC_OK) return st;
-    regenvc::LinearArgs la{a, w, bias, gate, out, lda, ldo, M, N, K, epilogue};
-    return regenvc::abi::launch_status(regenvc::launch_linear(la, static_cast<hipStream_t>(stream)), fn);
+    return run_linear("regenvc_linear_fwd", a, lda, w, bias, gate, out, ldo, M, N, K, epilogue, nullptr, 0, stream);
+}
+
+regenvc_status regenvc_linear_fwd_ws(const void *a, int64_t lda, const void *w, const void *bias, const float *gate,
+                                     void *out, int64_t ldo, int32_t M, int32_t N, int32_t K, int32_t epilogue,
+                                     void *workspace, int64_t workspace_bytes, void *stream)
+{
+    return run_linear("regenvc_linear_fwd_ws", a, lda, w, bias, gate, out, ldo, M, N, K, epilogue, workspace,
+                      workspace_bytes, stream);
+}
+
+regenvc_status regenvc_linear_workspace(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t n_cu,
+                                        int64_t *bytes)
+{
+    const char *fn = "regenvc_linear_workspace";
+    if (bytes == nullptr) return failf(REGENVC_ERR_INVALID_ARG, "%s: bytes is NULL", fn);
+    if (M < 0 || N < 0 || K < 0 || n_cu < 1)
+        return failf(REGENVC_ERR_INVALID_ARG, "%s: bad size (M=%d N=%d K=%d n_cu=%d)", fn, M, N, K, n_cu);
+    if (epilogue != REGENVC_EPI_BIAS && epilogue != REGENVC_EPI_BIAS_GELU && epilogue != REGENVC_EPI_GATED_RESIDUAL)
+        return failf(REGENVC_ERR_INVALID_ARG, "%s: unknown epilogue %d", fn, epilogue);
+    if (K % 64 != 0 || N % 16 != 0)
+        return failf(REGENVC_ERR_UNSUPPORTED, "%s: K=%d must be a multiple of 64, N=%d of 16", fn, K, N);
+    *bytes = (int64_t)regenvc::linear_workspace_bytes(M, N, K, epilogue, n_cu);
+    regenvc::abi::clear_error();
+    return REGENVC_OK;
 }
 
 regenvc_status regenvc_layer_norm_fwd(const float *x, int64_t ldx, void *y, int64_t ldy, const float *shift,
@@ -248,7 +299,8 @@ regenvc_status regenvc_dit_block_fwd(float *x, const float *e, const regenvc_dit
     auto linear = [&](const void *a, int64_t lda, const void *w, const void *bias, const float *gate, void *out,
                       int64_t ldo, int N, int K, int epi) {
         if (err != hipSuccess) return;
-        err = regenvc::launch_linear(regenvc::LinearArgs{a, w, bias, gate, out, lda, ldo, S, N, K, epi}, s);
+        err = regenvc::launch_linear(regenvc::LinearArgs{a, w, bias, gate, out, lda, ldo, S, N, K, epi,
+                                                         static_cast<float *>(scr.ptr), (int64_t)scr.bytes}, s);
     };
     auto norm = [&](const float *shift, const float *sc, const void *w, const void *b) {
         if (err != hipSuccess) return;

@@ -26,11 +26,28 @@ struct LinearArgs {
     int64_t lda, ldo;
     int32_t M, N, K;
     int32_t epi;
+    float *ws;         // split-K partials, or null: no split
+    int64_t ws_bytes;
 };
 
-// Tile rows of the launch the planner picks for this shape on n_cu CUs
-// (256 or 288; the tile is that many rows x 256 output channels).
-int linear_tile_rows(int M, int N, int n_cu);
+// Tile of a linear launch (rows x output channels per workgroup) and the
+// number of K ranges it is split into (f32 partials in the workspace, added
+// by a second kernel with the epilogue; 1: none).
+enum LinearTile : int32_t {
+    kTile256x256 = 0,
+    kTile160x256 = 1,
+    kTile192x192 = 2,
+    kTile128x128 = 3,
+    kTile64x128 = 4,
+    kTile288x256 = 5,
+};
+struct LinearPlan {
+    int32_t tile, splits;
+};
+// The plan of this shape on n_cu compute units with ws_bytes of workspace.
+LinearPlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes);
+// Workspace bytes that give a linear launch its full split (0: it does not split).
+size_t linear_workspace_bytes(int M, int N, int K, int epi, int n_cu);
 hipError_t launch_linear(const LinearArgs &a, hipStream_t stream);
 
 // Row normalization of x (f32 [rows, C], row stride ldx) into bf16 y (row

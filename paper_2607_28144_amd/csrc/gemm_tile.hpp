@@ -368,6 +368,397 @@ constexpr int lds_bytes()
     return ring > staging ? ring : staging;
 }
 
+// ---------------------------------------------------------------- four waves
+// The same product by four waves, one (or, for small tiles, two or three
+// workgroups') per SIMD, each owning (16 MB) rows x (16 NB) channels of a
+// (32 MB) x (32 NB) tile.
+//
+// What bounds it and why this form.  One 64-deep K step is 2 MB NB MFMAs of
+// 16-17 cycles per wave; beside them the LDS takes the step's copies at 64
+// bytes a cycle and serves the fragment reads at 128.  256 x 256: 2176 cycles
+// of MFMA against 2048 of LDS; 192 x 192: 1224 against 1536 (measured: 1474 a
+// step); 128 x 128: 544 against 1024 (1075).  The eight-wave tile (144 x 64
+// per wave) reads half as much again per MFMA: 2752 against 2304 (3228).
+// Both halves of a step (32 deep each) have their fragments
+// in registers before their MFMAs begin: the reads of a step's second half
+// run beside the MFMAs of its first, those of the next step's first half
+// beside the MFMAs of its second, so that nothing waits for LDS after the
+// step's one barrier.  A wave has its SIMD to itself: every cycle in which it
+// cannot issue is a cycle without MFMAs.  The loop therefore has no branch at
+// all (the copies of the last two steps read the last step's data again,
+// into stages nobody reads) and no vector address arithmetic (32-bit lane
+// offsets, scalar bases), and its copies are spread one per eight MFMAs: A's
+// over the first half, into a ring of three stages, W's over the second,
+// into a ring of two.  Measured on 36 workgroups of 256 x 256 x 8960: 137 us;
+// with a branch around the copies 174 us, one around each copy 248 us,
+// without any copies 135 us.  8192 x 8192 x 8192: 724 us (1520 TFLOP/s), the
+// eight-wave tile kernel 782-792 us.
+template <int MB_, int NB_, int AS_, int WPE_>
+struct Shape4 {
+    static constexpr int MB = MB_, NB = NB_;  // 16-row and 16-channel blocks per wave
+    static constexpr int AS = AS_;            // stages of the A ring (W's has two)
+    static constexpr int WPE = WPE_;          // waves per SIMD: workgroups per compute unit
+    static constexpr int BM = 32 * MB, BN = 32 * NB;
+    static constexpr int A_BYTES = BM * kRowBytes, W_BYTES = BN * kRowBytes;
+    static constexpr int LDS = AS * A_BYTES + 2 * W_BYTES;
+    static_assert(MB * NB <= 64 && (MB * NB) % 2 == 0 && (AS == 2 || AS == 3), "tile shape");
+    static_assert(LDS * WPE <= 160 * 1024, "the workgroups of one compute unit fit its LDS");
+};
+
+constexpr int kThreads4 = 256;
+
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// 16-byte HBM -> LDS copies, lane i to lds_base + 16 i (a wave-uniform
+// address): with a scalar base and a 32-bit lane offset, and with a 64-bit
+// lane address.  One wait state between the write of M0 and its use.
+__device__ __forceinline__ void lds_copy16_s(const void *base, uint32_t off, uint32_t lds_base)
+{
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(lds_base), "v"(off), "s"(base)
+                     : "m0");
+}
+__device__ __forceinline__ void lds_copy16_v(const void *ptr, uint32_t lds_base)
+{
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                     :
+                     : "s"(lds_base), "v"(ptr)
+                     : "m0");
+}
+#pragma clang diagnostic pop
+
+// Rows of a [rows, K] bf16 matrix (row stride ld elements) as a copy source:
+// copies read row r (clamped to the last one; those rows are never stored),
+// 16-byte chunk c, K step kt.  WIDE: strides for which the offsets within a
+// tile do not fit 32 bits.
+template <bool WIDE>
+struct Dense {
+    const uint16_t *p;
+    int64_t ld;
+    int rows;
+    int r0;
+    struct Row {
+        const char *ptr;
+        uint32_t off;
+    };
+    __device__ Row row(int r, int chunk) const
+    {
+        Row q;
+        const int64_t m = min(r0 + r, rows - 1);
+        if constexpr (WIDE) {
+            q.ptr = reinterpret_cast<const char *>(p + m * ld) + chunk * 16;
+            q.off = 0;
+        } else {
+            q.ptr = nullptr;
+            q.off = (uint32_t)(m - r0) * (uint32_t)ld * 2 + chunk * 16;
+        }
+        return q;
+    }
+    __device__ void copy(const Row &q, int kt, uint32_t lds) const
+    {
+        if constexpr (WIDE)
+            lds_copy16_v(q.ptr + (int64_t)kt * kRowBytes, lds);
+        else
+            lds_copy16_s(reinterpret_cast<const char *>(p + (int64_t)r0 * ld) + (int64_t)kt * kRowBytes, q.off, lds);
+    }
+};
+
+// Tile (row block, channel block) of workgroup bid among n_tiles: the
+// XCD-aware order of tile_body.
+__device__ __forceinline__ void tile_of(int bid, int tiles_n, int n_tiles, int &tm, int &tn)
+{
+    const int xcd = bid & 7, slot = bid >> 3;
+    const int tile = xcd * (n_tiles >> 3) + min(xcd, n_tiles & 7) + slot;
+    const int tiles_m = n_tiles / tiles_n;
+    const int group = tile / (kGroupM * tiles_n), in_group = tile - group * kGroupM * tiles_n;
+    const int gm = min(tiles_m - group * kGroupM, kGroupM);
+    tm = group * kGroupM + in_group % gm;
+    tn = in_group / gm;
+}
+
+// c += a b.  Tiles with one wave per SIMD keep up to 256 accumulation
+// registers: written as an instruction whose result is tied to its addend,
+// since the allocator otherwise renames the accumulators and moves them back
+// on every K step (116 to 608 register moves per step of 128 MFMAs).  The
+// compiler inserts no wait states around it: its operands come from LDS
+// reads (counted), and mma4 ends with the wait states that a vector read of
+// the accumulators needs.
+template <class S>
+__device__ __forceinline__ void mfma_into(f32x4 &c, bf16x8 a, bf16x8 b)
+{
+    if constexpr (S::WPE == 1)
+        __asm__("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+    else
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// The K loop over steps [k0, k1) (k1 > k0): acc[nb][mb][i] = the sum for row
+// 16 MB wm + 16 mb + x and channel 16 NB wn + 16 nb + 4 g + i of the tile,
+// lane = 16 g + x.  On return no copy is in flight.
+template <class S, class ASrc, class WSrc>
+__device__ __forceinline__ void mma4(const ASrc &as, const WSrc &ws, int k0, int k1, char *smem,
+                                     f32x4 (&acc)[S::NB][S::MB])
+{
+    constexpr int MB = S::MB, NB = S::NB, AS = S::AS;
+    constexpr int AB = S::A_BYTES, WB = S::W_BYTES;
+    constexpr int AP = AB / 4096, WP = WB / 4096;  // copies per wave and step
+    constexpr int NM = MB * NB, NF = MB + NB;
+    constexpr uint32_t W0 = AS * AB;               // LDS: the A ring, then the W ring
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1, g = lane >> 4, x = lane & 15;
+
+    typename ASrc::Row arow[AP];
+    typename WSrc::Row wrow[WP];
+#pragma unroll
+    for (int i = 0; i < AP; ++i) {
+        const int r = (wave * AP + i) * 8 + (lane >> 3);
+        arow[i] = as.row(r, swz(r, lane & 7));
+    }
+#pragma unroll
+    for (int i = 0; i < WP; ++i) {
+        const int r = (wave * WP + i) * 8 + (lane >> 3);
+        wrow[i] = ws.row(r, swz(r, lane & 7));
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char *)smem;
+    const uint32_t la0 = __builtin_amdgcn_readfirstlane(lds0 + wave * AP * 1024);
+    const uint32_t lw0 = __builtin_amdgcn_readfirstlane(lds0 + wave * WP * 1024);
+    auto copy_a = [&](int i, uint32_t so, int kt) { as.copy(arow[i], kt, la0 + so + i * 1024); };
+    auto copy_w = [&](int i, uint32_t so, int kt) { ws.copy(wrow[i], kt, lw0 + so + i * 1024); };
+
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    bf16x8 fa[2][MB], fw[2][NB];
+    const int ra = wm * 16 * MB + x, rw = wn * 16 * NB + x;
+    // fragment f (W's first) of half ks from A stage ao and W stage wo
+    auto rd = [&](uint32_t ao, uint32_t wo, int ks, int f) {
+        const lds_char *s = (const lds_char *)smem;
+        if (f < NB)
+            fw[ks][f] = *(const lds_bf16x8 *)(s + wo + (rw + f * 16) * kRowBytes + swz(rw, ks * 4 + g) * 16);
+        else
+            fa[ks][f - NB] = *(const lds_bf16x8 *)(s + ao + (ra + (f - NB) * 16) * kRowBytes + swz(ra, ks * 4 + g) * 16);
+    };
+    auto mfma2 = [&](int ks, int i) {
+#pragma unroll
+        for (int j = i; j < i + 2; ++j) mfma_into<S>(acc[j % NB][j / NB], fw[ks][j % NB], fa[ks][j / NB]);
+    };
+
+    const int kl = k1 - 1;
+#pragma unroll
+    for (int i = 0; i < AP; ++i) copy_a(i, 0, k0);
+#pragma unroll
+    for (int i = 0; i < WP; ++i) copy_w(i, W0, k0);
+#pragma unroll
+    for (int i = 0; i < AP; ++i) copy_a(i, AB, min(k0 + 1, kl));
+#pragma unroll
+    for (int i = 0; i < WP; ++i) copy_w(i, W0 + WB, min(k0 + 1, kl));
+    __asm__ volatile("s_waitcnt vmcnt(%0)" : : "n"(AP + WP) : "memory");
+    __builtin_amdgcn_s_barrier();
+    __asm__ volatile("" : : : "memory");
+#pragma unroll
+    for (int f = 0; f < NF; ++f) rd(0, W0, 0, f);
+
+    constexpr int RD = NM * 3 / 4;  // a half's reads are spread over this many MFMAs
+    uint32_t ao = 0, wo = W0;
+    for (int kt = k0; kt < k1; ++kt) {
+        const int k2 = min(kt + 2, kl);
+        const uint32_t ao1 = ao + AB == AS * AB ? 0 : ao + AB, wo1 = wo == W0 ? W0 + WB : W0;
+        const uint32_t ao2 = ao1 + AB == AS * AB ? 0 : ao1 + AB;
+        // first half; with three A stages, A of step kt + 2 goes where step
+        // kt - 1's was (its last read lies before the previous barrier)
+#pragma unroll
+        for (int i = 0; i < NM; i += 2) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                if (f * RD / NF / 2 * 2 == i) rd(ao, wo, 1, f);
+            if constexpr (AS == 3) {
+#pragma unroll
+                for (int l = 0; l < AP; ++l)
+                    if ((l * NM / AP + 2) / 2 * 2 == i) copy_a(l, ao2, k2);
+            }
+            mfma2(0, i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // step kt + 1 has landed, and every wave has read all of step kt
+        __asm__ volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(AS == 3 ? AP : 0) : "memory");
+        __builtin_amdgcn_s_barrier();
+        __asm__ volatile("" : : : "memory");
+        // second half; W of step kt + 2 (and A with two stages) replaces step kt's
+        constexpr int NC = AS == 3 ? WP : AP + WP;
+#pragma unroll
+        for (int i = 0; i < NM; i += 2) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                if (f * RD / NF / 2 * 2 == i) rd(ao1, wo1, 0, f);
+#pragma unroll
+            for (int l = 0; l < NC; ++l)
+                if (l * RD / NC / 2 * 2 == i) {
+                    if (AS == 3 || l >= AP)
+                        copy_w(AS == 3 ? l : l - AP, wo, k2);
+                    else
+                        copy_a(l, ao, k2);
+                }
+            mfma2(1, i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        ao = ao1, wo = wo1;
+    }
+    // wait states between the last MFMAs and the first read of their results
+    if constexpr (S::WPE == 1) {
+        __asm__ volatile("s_nop 15\n\ts_nop 15" : : : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    wait_all_copies();
+}
+
+// Activation of an epilogue.
+template <int EPI>
+__device__ __forceinline__ float activate(float y)
+{
+    return EPI == kBiasGelu ? gelu_tanh(y) : EPI == kBiasSilu ? silu(y) : y;
+}
+
+__device__ __forceinline__ f32x4 load_bias4(const uint16_t *bias, int n)
+{
+    f32x4 bv = {0.f, 0.f, 0.f, 0.f};
+    if (bias != nullptr) {
+        const uint64_t b4 = *reinterpret_cast<const uint64_t *>(bias + n);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bv[i] = bf((uint16_t)(b4 >> (16 * i)));
+    }
+    return bv;
+}
+
+// Writes a tile (m0, n0) from the accumulators of mma4.  A tile of whole
+// width with 16-byte rows goes through the idle LDS, so that each store
+// writes whole 16-byte chunks of consecutive rows (the fp32 residual in two
+// halves of the channels); other tiles and split-K partials are written
+// straight from the accumulators.  sp: K range of a kPartial launch.
+template <class S, int EPI>
+__device__ __forceinline__ void store4(const Out &o, int m0, int n0, int sp, char *smem, f32x4 (&acc)[S::NB][S::MB])
+{
+    constexpr int MB = S::MB, NB = S::NB, BM = S::BM, BN = S::BN;
+    constexpr bool BF16_OUT = EPI == kBias || EPI == kBiasGelu || EPI == kBiasSilu;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1, g = lane >> 4, x = lane & 15;
+    const bool whole = n0 + BN <= o.N && (reinterpret_cast<uintptr_t>(o.out) & 15) == 0 && (o.ldo & 7) == 0;
+    if constexpr (BF16_OUT) {
+        if (whole) {
+            constexpr int CH = BN / 8;  // 16-byte chunks per staged row, chunk c of row r at c ^ (r & 7)
+            static_assert(CH % 8 == 0 && (BM * CH) % kThreads4 == 0 && BM * BN * 2 <= S::LDS, "staging shape");
+            __syncthreads();  // every wave is done with the rings
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const f32x4 bv = load_bias4(o.bias, n0 + wn * (16 * NB) + nb * 16 + 4 * g);
+                const int c = wn * 2 * NB + nb * 2 + g / 2;
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const int r = wm * 16 * MB + mb * 16 + x;
+                    const f32x4 y = acc[nb][mb] + bv;
+                    bf16x4 w;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) w[i] = (__bf16)activate<EPI>(y[i]);
+                    *(__attribute__((address_space(3))) bf16x4 *)((lds_char *)smem + r * (BN * 2) +
+                                                                 ((c ^ (r & 7)) * 16) + (g & 1) * 8) = w;
+                }
+            }
+            __syncthreads();
+#pragma unroll 8
+            for (int it = 0; it < BM * CH / kThreads4; ++it) {
+                const int id = it * kThreads4 + (int)threadIdx.x;
+                const int r = id / CH, c = id % CH;
+                const bf16x8 v = *(const lds_bf16x8 *)((const lds_char *)smem + r * (BN * 2) + ((c ^ (r & 7)) * 16));
+                if (m0 + r < o.M)
+                    *reinterpret_cast<bf16x8 *>(static_cast<uint16_t *>(o.out) + (int64_t)(m0 + r) * o.ldo + n0 +
+                                                c * 8) = v;
+            }
+            return;
+        }
+    }
+    if constexpr (EPI == kGatedRes) {
+        if (whole) {
+            constexpr int HALF = BN / 2;  // channels per pass: one wave column
+            constexpr int CH = HALF / 4;  // 16-byte chunks per staged row
+            constexpr int NT = BM * CH / kThreads4, BT = NT % 8 == 0 ? 8 : NT % 6 == 0 ? 6 : NT % 5 == 0 ? 5 : 4;
+            static_assert(CH % 8 == 0 && (BM * CH) % kThreads4 == 0 && BM * HALF * 4 <= S::LDS && NT % BT == 0,
+                          "staging shape");
+#pragma unroll
+            for (int pass = 0; pass < 2; ++pass) {
+                __syncthreads();  // the rings (first pass) or the previous half are no longer read
+                if (wn == pass) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const f32x4 bv = load_bias4(o.bias, n0 + wn * HALF + nb * 16 + 4 * g);
+                        const int c = nb * 4 + g;
+#pragma unroll
+                        for (int mb = 0; mb < MB; ++mb) {
+                            const int r = wm * 16 * MB + mb * 16 + x;
+                            *(__attribute__((address_space(3))) f32x4 *)((lds_char *)smem + r * (HALF * 4) +
+                                                                        ((c ^ (r & 7)) * 16)) = acc[nb][mb] + bv;
+                        }
+                    }
+                }
+                __syncthreads();
+                // BT chunks of the residual are requested before the first is used
+                for (int t0 = 0; t0 < NT; t0 += BT) {
+                    f32x4 res[BT];
+#pragma unroll
+                    for (int t = 0; t < BT; ++t) {
+                        const int id = (t0 + t) * kThreads4 + (int)threadIdx.x;
+                        const int r = id / CH, n = n0 + pass * HALF + (id % CH) * 4;
+                        res[t] = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(o.out) +
+                                                                  (int64_t)min(m0 + r, o.M - 1) * o.ldo + n);
+                    }
+#pragma unroll
+                    for (int t = 0; t < BT; ++t) {
+                        const int id = (t0 + t) * kThreads4 + (int)threadIdx.x;
+                        const int r = id / CH, c = id % CH, n = n0 + pass * HALF + c * 4;
+                        const f32x4 y = *(const __attribute__((address_space(3))) f32x4 *)((const lds_char *)smem +
+                                                                                         r * (HALF * 4) +
+                                                                                         ((c ^ (r & 7)) * 16));
+                        const f32x4 gv = o.gate != nullptr ? *reinterpret_cast<const f32x4 *>(o.gate + n)
+                                                           : f32x4{1.f, 1.f, 1.f, 1.f};
+                        if (m0 + r < o.M)
+                            *reinterpret_cast<f32x4 *>(static_cast<float *>(o.out) + (int64_t)(m0 + r) * o.ldo + n) =
+                                res[t] + gv * y;
+                    }
+                }
+            }
+            return;
+        }
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int n = n0 + wn * (16 * NB) + nb * 16 + 4 * g;
+        if (n >= o.N) continue;
+        const f32x4 bv = EPI == kPartial ? f32x4{0.f, 0.f, 0.f, 0.f} : load_bias4(o.bias, n);
+        f32x4 gv = {1.f, 1.f, 1.f, 1.f};
+        if (EPI == kGatedRes && o.gate != nullptr) gv = *reinterpret_cast<const f32x4 *>(o.gate + n);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int m = m0 + wm * 16 * MB + mb * 16 + x;
+            if (m >= o.M) continue;
+            const f32x4 y = acc[nb][mb] + bv;
+            if constexpr (EPI == kPartial) {
+                *reinterpret_cast<f32x4 *>(static_cast<float *>(o.out) + ((int64_t)sp * o.M + m) * o.ldo + n) = y;
+            } else if constexpr (EPI == kGatedRes) {
+                f32x4 *p = reinterpret_cast<f32x4 *>(static_cast<float *>(o.out) + (int64_t)m * o.ldo + n);
+                *p = *p + gv * y;
+            } else {
+                bf16x4 w;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[i] = (__bf16)activate<EPI>(y[i]);
+                *reinterpret_cast<bf16x4 *>(static_cast<uint16_t *>(o.out) + (int64_t)m * o.ldo + n) = w;
+            }
+        }
+    }
+}
+
 // XCD-aware tile count helpers for the launchers.
 inline int tiles_along(int n, int b)
 {

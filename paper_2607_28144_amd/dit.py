@@ -36,11 +36,34 @@ def _vec(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, n: int) -> Op
     return t.data_ptr()
 
 
+_N_CU = {}   # device index -> compute units
+_NEED = {}   # (device index, shape, epilogue) -> workspace bytes of a linear layer
+
+
+def linear_workspace_bytes(M: int, N: int, K: int, epilogue: str, device) -> int:
+    """Workspace bytes of the split-K form of one linear layer on this device
+    (regenvc_linear_workspace; host-only, 0 when it does not split)."""
+    idx = torch.device(device).index
+    idx = torch.cuda.current_device() if idx is None else idx
+    need = _NEED.get((idx, M, N, K, epilogue))
+    if need is None:
+        if idx not in _N_CU:
+            _N_CU[idx] = torch.cuda.get_device_properties(idx).multi_processor_count
+        out = ctypes.c_int64()
+        st = _lib.load().regenvc_linear_workspace(M, N, K, EPI[epilogue], _N_CU[idx], ctypes.byref(out))
+        need = out.value if st == _lib.OK else 0  # a shape the call itself refuses: let it say so
+        if len(_NEED) >= 4096:
+            _NEED.clear()
+        _NEED[(idx, M, N, K, epilogue)] = need
+    return need
+
+
 def linear_fwd(a: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor] = None, epilogue: str = "bias",
                gate: Optional[torch.Tensor] = None, out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """y = a w^T (+ bias) with a fused epilogue (regenvc_linear_fwd):
+    """y = a w^T (+ bias) with a fused epilogue (regenvc_linear_fwd_ws):
     'bias' -> bf16 out, 'bias_gelu' -> bf16 gelu_tanh(y), 'gated_residual' ->
-    out (float32, required) += gate * y."""
+    out (float32, required) += gate * y.  The workspace of the split-K form is
+    a torch allocation on the current stream."""
     M, K = a.shape
     N = w.shape[0]
     lda = _rows(a, "a", torch.bfloat16)
@@ -52,10 +75,12 @@ def linear_fwd(a: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor] = 
             raise ValueError("the gated-residual epilogue needs out (the float32 residual stream)")
         out = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
     ldo = _rows(out, "out", torch.float32 if epi == 2 else torch.bfloat16)
-    st = _lib.load().regenvc_linear_fwd(a.data_ptr(), lda, w.data_ptr(), _vec(bias, "bias", torch.bfloat16, N),
-                                        _vec(gate, "gate", torch.float32, N), out.data_ptr(), ldo, M, N, K, epi,
-                                        _stream(a.device))
-    _lib.check(st, "regenvc_linear_fwd")
+    need = linear_workspace_bytes(M, N, K, epilogue, a.device)
+    ws = torch.empty(need, dtype=torch.uint8, device=a.device) if need > 0 else None
+    st = _lib.load().regenvc_linear_fwd_ws(a.data_ptr(), lda, w.data_ptr(), _vec(bias, "bias", torch.bfloat16, N),
+                                           _vec(gate, "gate", torch.float32, N), out.data_ptr(), ldo, M, N, K, epi,
+                                           ws.data_ptr() if ws is not None else None, need, _stream(a.device))
+    _lib.check(st, "regenvc_linear_fwd_ws")
     return out
 
 

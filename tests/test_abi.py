@@ -354,3 +354,31 @@ def test_chunked_partials_plan_query(lib):
     b = (ctypes.c_int32 * 3)(0, 10, 10)
     expect(lib, lib.regenvc_attn_partials_plan_query(1, 5, 10920, 2, b, 128, 256, ctypes.byref(plan)),
            _lib.ERR_INVALID_ARG, "empty")
+
+
+def test_linear_workspace(lib):
+    """The split-K workspace: none where the tiles fill the chip or K is
+    short, whole f32 planes of the output otherwise; refused sizes."""
+    def need(M, N, K, epi=0, n_cu=256):
+        b = ctypes.c_int64(-1)
+        assert lib.regenvc_linear_workspace(M, N, K, epi, n_cu, ctypes.byref(b)) == _lib.OK
+        return b.value
+    assert need(10920, 1536, 8960, 2) == 0 and need(300, 1536, 64) == 0
+    assert need(0, 1536, 8960) == 0 and need(300, 0, 8960) == 0 and need(300, 1536, 0) == 0
+    for M in (1, 65, 300, 1365):
+        for epi in (0, 1, 2):
+            n = need(M, 1536, 8960, epi)
+            assert n % (M * 1536 * 4) == 0 and 2 <= n // (M * 1536 * 4) <= 8
+    b = ctypes.c_int64()
+    for args in [(-1, 16, 64, 0, 256), (1, -16, 64, 0, 256), (1, 16, -64, 0, 256), (1, 16, 64, 0, 0), (1, 16, 64, 3, 256)]:
+        assert lib.regenvc_linear_workspace(*args, ctypes.byref(b)) == _lib.ERR_INVALID_ARG
+    assert lib.regenvc_linear_workspace(1, 16, 65, 0, 256, ctypes.byref(b)) == _lib.ERR_UNSUPPORTED
+    assert lib.regenvc_linear_workspace(1, 17, 64, 0, 256, ctypes.byref(b)) == _lib.ERR_UNSUPPORTED
+    assert lib.regenvc_linear_workspace(1, 16, 64, 0, 256, None) == _lib.ERR_INVALID_ARG
+    # the call itself: a negative size, a misaligned and an overlapping workspace
+    call = lambda ws, n: lib.regenvc_linear_fwd_ws(FAKE, 64, FAKE + (1 << 20), None, None, FAKE + (2 << 20), 16,  # noqa: E731
+                                                   4, 16, 64, 0, ws, n, None)
+    assert call(FAKE + (3 << 20), -1) == _lib.ERR_INVALID_ARG
+    assert call(FAKE + (3 << 20) + 128, 4096) == _lib.ERR_UNSUPPORTED
+    for base in (FAKE, FAKE + (1 << 20), FAKE + (2 << 20)):
+        assert call(base, 4096) == _lib.ERR_INVALID_ARG

@@ -99,6 +99,58 @@ def test_linear_epilogues(M, N, K):
                 np.abs(gate) * slack + 2.0 ** -22 * (np.abs(x0) + np.abs(gate * y)) + 1e-7)
 
 
+# one shape or more per tile of the plan, with ragged last rows and channels,
+# the shortest K each can have, and K splits with uneven ranges
+@pytest.mark.parametrize("M,N,K", [(1, 16, 64), (65, 1552, 128), (513, 1536, 192),             # 64 x 128
+                                   (5461, 272, 64), (300, 4624, 1536), (1365, 1536, 1536),     # 128 x 128
+                                   (1001, 8960, 1536), (5460, 1552, 1536),                     # 160 x 256
+                                   (1365, 8976, 1536),                                         # 256 x 256
+                                   (5460, 1536, 1536),                                         # 192 x 192
+                                   (1365, 1552, 8960), (64, 1536, 8960), (700, 1536, 8896)])   # K split
+def test_linear_tiles(M, N, K):
+    test_linear_epilogues(M, N, K)
+
+
+def test_linear_wide_row_stride():
+    """Rows so far apart that a tile's offsets leave 32 bits."""
+    M, N, K, ld = 300, 272, 192, 1 << 23
+    rng = np.random.default_rng(5)
+    a, w = bits(rng, (M, K)), bits(rng, (N, K), 0.02)
+    wide = torch.zeros((M - 1) * ld + K, dtype=torch.bfloat16, device="cuda")
+    da = wide.as_strided((M, K), (ld, 1))
+    da.copy_(dev_bits(a))
+    dw = dev_bits(w)
+    got = kern().linear_fwd(da, dw)
+    assert torch.equal(got, kern().linear_fwd(da.contiguous(), dw))  # one tile shape, one K order
+
+
+def test_linear_split_workspace_sizes():
+    """The split-K form under a workspace that is missing, too small for any
+    split, enough for some and enough for all ranges."""
+    import ctypes
+    from paper_2607_28144_amd import _lib
+    M, N, K = 300, 1536, 8960
+    rng = np.random.default_rng(6)
+    a, w = bits(rng, (M, K)), bits(rng, (N, K), 0.02)
+    y = odit.gemm(odit.widen(a), odit.widen(w), np.zeros(N))
+    slack = 2 * ACC * (np.abs(odit.widen(a)) @ np.abs(odit.widen(w)).T)
+    da, dw = dev_bits(a), dev_bits(w)
+    full = kern().linear_workspace_bytes(M, N, K, "bias", da.device)
+    plane = M * N * 4
+    assert full >= 2 * plane
+    lib = _lib.load()
+    for need in (0, 256, 2 * plane, 3 * plane + 256, full):
+        ws = torch.full((max(need, 1) + 512,), 0x7F, dtype=torch.uint8, device="cuda")
+        out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+        st = lib.regenvc_linear_fwd_ws(da.data_ptr(), K, dw.data_ptr(), None, None, out.data_ptr(), N, M, N, K, 0,
+                                       ws.data_ptr() if need else None, need,
+                                       ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        _lib.check(st, "regenvc_linear_fwd_ws")
+        torch.cuda.synchronize()
+        assert bool((ws[need:] == 0x7F).all()), "written past the workspace"
+        check_bound(f"linear split, workspace {need}", host(out), y, ULP * np.abs(y) + slack)
+
+
 def test_linear_without_bias_or_gate_into_a_strided_output():
     """No bias, no gate (1), the output a column slice of a wider buffer."""
     rng = np.random.default_rng(5)
