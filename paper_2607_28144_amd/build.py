@@ -4,6 +4,7 @@ Run as ``python -m paper_2607_28144_amd.build``; it compiles every time it is
 called.  Packed-fp32 VALU instructions are switched off for all device code.
 """
 import os
+import re
 import subprocess
 import sys
 import tempfile
@@ -50,12 +51,22 @@ def build(verbose: bool = False) -> str:
         msgs = [ln for ln in (res.stdout + res.stderr).splitlines() if "packed-fp32-ops" not in ln]
         if res.returncode != 0:
             raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
+        remarks = [ln for ln in msgs if "kernel-resource-usage" in ln]
+        msgs = [ln for ln in msgs if "kernel-resource-usage" not in ln and not re.match(r"^\s*\d*\s*\||^\s*\^", ln)]
         if verbose and msgs:
             print("\n".join(msgs), flush=True)
+        return remarks
 
     def compile_one(name, obj):
         extra = ["-mllvm", "-amdgpu-mfma-vgpr-form"] if name in VGPR_FORM else []
-        run([hipcc()] + flags + extra + ["-c", "-o", obj, os.path.join(CSRC, name)])
+        kernel = ""
+        for ln in run([hipcc()] + flags + extra + ["-Rpass-analysis=kernel-resource-usage", "-c", "-o", obj,
+                                                   os.path.join(CSRC, name)]):
+            if "Function Name:" in ln:
+                kernel = ln
+            # tiles whose MFMAs are instructions of their own: no spill may touch their accumulators
+            elif "Shape4" in kernel and "Spill" in ln and not re.search(r"Spill: 0\b", ln):
+                raise RuntimeError(f"{name}: a four-wave tile kernel spills: {kernel} {ln}")
 
     with tempfile.TemporaryDirectory() as tmp:
         objs = [os.path.join(tmp, s + ".o") for s in SOURCES]

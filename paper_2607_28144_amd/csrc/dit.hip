@@ -10,12 +10,9 @@
 // 288 x 256, K split over workgroups where the tiles are few (linear_plan).
 #include "dit_kernels.hpp"
 
-#include <math.h>
-
-#include <algorithm>
-
 #include "attn_kernels.hpp"
 #include "gemm_tile.hpp"
+#include "tile_plan.hpp"
 
 namespace regenvc {
 namespace {
@@ -356,61 +353,36 @@ hipError_t launch_linear4(const LinearArgs &a, int splits, hipStream_t stream)
 
 }  // namespace
 
-// The tile and K split with the smallest estimated time.  A launch is whole
-// rounds of n_cu workgroups and one last, partly filled round; a workgroup
-// costs a fixed time (launch, first copies, epilogue) and a time per 64-deep
-// K step, measured on launches of at most one round (in us; 300 x 1536 x 1536
-// to 2000 x 1536 x 8960); full rounds run slower by `load`, at the clock that
-// the power limit leaves.  A split adds the second kernel: its launch, and the
-// partials written, read and reduced at memory speed.  Over 14 row counts
-// from 64 to 10920 of the block's five layers the choice is on average 1.2 %
-// slower than the best of all tiles and splits.  Measured, 256 x 256 by eight
-// waves before: 1365 x 1536 x 8960 203 -> 49 us (192 x 192 in four ranges),
+// The tile and K split of a linear layer, by plan_tiles; the constants are
+// fitted to 14 row counts from 64 to 10920 of the block's five layers (the
+// choice is on average 1.2 % slower than the best of all tiles and splits).
+// Measured, against 256 x 256 or 288 x 256 by eight waves:
+// 1365 x 1536 x 8960 203 -> 49 us (192 x 192 in four ranges),
 // 1560 x 4608 x 1536 39.7 -> 25.0 us (128 x 128), 10920 x 8960 x 1536 with
 // GELU 291 -> 270 us (256 x 256 by four waves); 10920 x 4608 and 10920 x 1536
 // stay with 288 x 256 by eight waves (138 and 46.7 us; the best other tile
 // 143 and 50.2: 228 tiles of 288 rows are one round where 43 row blocks of
 // 256 need 258 tiles).
-LinearPlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes)
+TilePlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes)
 {
-    struct Cost {
-        int32_t tile, bm, bn;
-        float step, fixed[3], load;  // fixed: by epilogue
-        bool splits;
+    // fixed times by tile and epilogue
+    static const double kFixed[6][3] = {{8.3, 13.0, 20.0}, {6.2, 9.0, 14.0}, {5.8, 8.2, 13.2},
+                                        {1.0, 2.3, 4.0},   {1.0, 2.0, 2.8},  {5.0, 9.0, 9.0}};
+    const TileCost costs[] = {
+        {kTile288x256, 288, 256, kFixed[5][epi], 0.0, 1.30, 1.32, false},
+        {kTile256x256, 256, 256, kFixed[0][epi], kFixed[0][0], 0.99, 1.32, true},
+        {kTile160x256, 160, 256, kFixed[1][epi], kFixed[1][0], 0.668, 1.32, true},
+        {kTile192x192, 192, 192, kFixed[2][epi], kFixed[2][0], 0.645, 1.32, true},
+        {kTile128x128, 128, 128, kFixed[3][epi], kFixed[3][0], 0.448, 1.02, true},
+        {kTile64x128, 64, 128, kFixed[4][epi], kFixed[4][0], 0.43, 1.02, true},
     };
-    static const Cost kCosts[] = {
-        {kTile256x256, 256, 256, 0.99f, {8.3f, 13.f, 20.f}, 1.32f, true},
-        {kTile160x256, 160, 256, 0.668f, {6.2f, 9.f, 14.f}, 1.32f, true},
-        {kTile192x192, 192, 192, 0.645f, {5.8f, 8.2f, 13.2f}, 1.32f, true},
-        {kTile128x128, 128, 128, 0.448f, {1.0f, 2.3f, 4.0f}, 1.02f, true},
-        {kTile64x128, 64, 128, 0.43f, {1.0f, 2.0f, 2.8f}, 1.02f, true},
-        {kTile288x256, 288, 256, 1.30f, {5.f, 9.f, 9.f}, 1.32f, false},
-    };
-    const int nk = K / kBK;
-    const int64_t plane = (int64_t)M * N * (int64_t)sizeof(float);
-    LinearPlan best{kTile288x256, 1};
-    double best_t = INFINITY;
-    for (const Cost &c : kCosts) {
-        const int64_t tiles = ((int64_t)M + c.bm - 1) / c.bm * (((int64_t)N + c.bn - 1) / c.bn);
-        const int max_splits = c.splits ? std::min(8, nk / 8) : 1;
-        for (int s = 1; s <= std::max(1, max_splits); ++s) {
-            if (s > 1 && (s * plane > ws_bytes || tiles * s > 2 * n_cu)) break;
-            if (tiles > 0x7fffffff / 8) break;
-            const double one = c.fixed[s > 1 ? (int)kEpiBias : epi] + (double)((nk + s - 1) / s) * c.step;
-            const int64_t full = tiles * s / n_cu, rest = tiles * s % n_cu;
-            double t = full * one * c.load;
-            if (rest > 0) t += one * (1.0 + (c.load - 1.0) * (double)rest / n_cu);
-            if (s > 1) t += 8.5 + ((double)plane * 2 * s + (double)M * N * (epi == kEpiGatedRes ? 8 : 2)) / 5.0e6;
-            if (t < best_t) best_t = t, best = LinearPlan{c.tile, s};
-        }
-    }
-    return best;
+    return plan_tiles(costs, SplitCost{8.5, 5.0e6, epi == kEpiGatedRes ? 8 : 2}, M, N, K / kBK, n_cu, ws_bytes);
 }
 
 size_t linear_workspace_bytes(int M, int N, int K, int epi, int n_cu)
 {
     if (M == 0 || N == 0 || K == 0) return 0;
-    const LinearPlan p = linear_plan(M, N, K, epi, n_cu, INT64_MAX);
+    const TilePlan p = linear_plan(M, N, K, epi, n_cu, INT64_MAX);
     return p.splits > 1 ? (size_t)p.splits * M * N * sizeof(float) : 0;
 }
 
@@ -418,7 +390,7 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
 {
     if (a.M == 0 || a.N == 0) return hipSuccess;
     if (a.K == 0 || a.lda >= kWideStride || a.K >= kWideStride) return launch_linear4<Tile128x128, true>(a, 1, stream);
-    const LinearPlan p = linear_plan(a.M, a.N, a.K, a.epi, device_cu_count(), a.ws != nullptr ? a.ws_bytes : 0);
+    const TilePlan p = linear_plan(a.M, a.N, a.K, a.epi, device_cu_count(), a.ws != nullptr ? a.ws_bytes : 0);
     switch (p.tile) {
     case kTile256x256: return launch_linear4<Tile256x256>(a, p.splits, stream);
     case kTile160x256: return launch_linear4<Tile160x256>(a, p.splits, stream);

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "tile_plan.hpp"
+
 namespace regenvc {
 
 // Epilogue of a linear layer y = a W^T (+ bias), applied per output element:
@@ -41,11 +43,8 @@ enum LinearTile : int32_t {
     kTile64x128 = 4,
     kTile288x256 = 5,
 };
-struct LinearPlan {
-    int32_t tile, splits;
-};
 // The plan of this shape on n_cu compute units with ws_bytes of workspace.
-LinearPlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes);
+TilePlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes);
 // Workspace bytes that give a linear launch its full split (0: it does not split).
 size_t linear_workspace_bytes(int M, int N, int K, int epi, int n_cu);
 hipError_t launch_linear(const LinearArgs &a, hipStream_t stream);

@@ -1,8 +1,9 @@
-// The bf16 MFMA tile kernel shared by the linear layers of the diffusion
-// block (dense rows) and the VAE's causal 3D convolution (rows gathered as
-// an implicit GEMM): out[m][n] = epilogue(sum_k A[m][k] W[n][k]).
+// The bf16 MFMA tile kernels of the linear layers of the diffusion block
+// (dense rows) and of the VAE's causal 3D convolution (rows gathered as an
+// implicit GEMM): out[m][n] = epilogue(sum_k A[m][k] W[n][k]).  Four waves per
+// tile (mma4, store4) for most shapes; eight (tile_body) for tiles of 288 rows.
 //
-// Workgroup = 8 waves (two per SIMD) = one BM x BN output tile, BN = 16 NB
+// Eight waves.  Workgroup = 8 waves (two per SIMD) = one BM x BN output tile, BN = 16 NB
 // WN; the waves form an (8 / WN) x WN grid, each owning (BM / (8 / WN)) rows
 // x 16 NB channels on v_mfma_f32_16x16x32_bf16.  The product is formed
 // transposed, C^T = W A^T, so that a lane's accumulator holds four
@@ -104,10 +105,24 @@ __device__ __forceinline__ float bf(uint16_t b)
     return __uint_as_float(((uint32_t)b) << 16);
 }
 
-// One BM x BN output tile.  The launch has n_tiles workgroups per K slice;
-// with EPI == kPartial it has o.splits slices (workgroup s * n_tiles + t:
-// tile t over the s-th of o.splits contiguous ranges of K steps), each
-// writing its partial sums to its own f32 [M][ldo] plane of o.out.
+// Tile (row block, channel block) of workgroup bid among n_tiles, XCD-aware:
+// workgroup i runs on XCD i % 8; XCD x takes a contiguous range of tiles.
+// Tiles are numbered in groups of kGroupM row blocks swept across the channel
+// blocks (row block fastest), so the ~32 tiles resident on an XCD at a time
+// cover about 4 row blocks x 8 channel blocks: each A row block and W block
+// they read serves several of them from the XCD's L2.
+__device__ __forceinline__ void tile_of(int bid, int tiles_n, int n_tiles, int &tm, int &tn)
+{
+    const int xcd = bid & 7, slot = bid >> 3;
+    const int tile = xcd * (n_tiles >> 3) + min(xcd, n_tiles & 7) + slot;
+    const int tiles_m = n_tiles / tiles_n;
+    const int group = tile / (kGroupM * tiles_n), in_group = tile - group * kGroupM * tiles_n;
+    const int gm = min(tiles_m - group * kGroupM, kGroupM);
+    tm = group * kGroupM + in_group % gm;
+    tn = in_group / gm;
+}
+
+// One BM x BN output tile of eight waves.
 template <int BM, int WN, int EPI, class ASrc, int NB = 4>
 __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int tiles_n, int n_tiles, char *smem)
 {
@@ -129,20 +144,8 @@ __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int ti
     const int wm = wave / WN, wn = wave % WN;
     const int g = lane >> 4, x = lane & 15;
 
-    // XCD-aware tile: workgroup i runs on XCD i % 8; XCD x takes a contiguous
-    // range of tiles.  Tiles are numbered in groups of kGroupM row blocks
-    // swept across the channel blocks (row block fastest), so the ~32 tiles
-    // resident on an XCD at a time cover about 4 row blocks x 8 channel
-    // blocks: each A row block and W block they read serves several of them
-    // from the XCD's L2.
-    const int sp = EPI == kPartial ? (int)blockIdx.x / n_tiles : 0;  // K slice
-    const int bid = EPI == kPartial ? (int)blockIdx.x - sp * n_tiles : (int)blockIdx.x;
-    const int xcd = bid & 7, slot = bid >> 3;
-    const int tile = xcd * (n_tiles >> 3) + min(xcd, n_tiles & 7) + slot;
-    const int tiles_m = n_tiles / tiles_n;
-    const int group = tile / (kGroupM * tiles_n), in_group = tile - group * kGroupM * tiles_n;
-    const int gm = min(tiles_m - group * kGroupM, kGroupM);
-    const int tm = group * kGroupM + in_group % gm, tn = in_group / gm;
+    int tm, tn;
+    tile_of((int)blockIdx.x, tiles_n, n_tiles, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
 
     // this lane's copies: instruction j of a tile covers its rows 8j..8j+7;
@@ -181,12 +184,10 @@ __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int ti
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const int nk_all = o.K / kBK;
-    const int k_begin = EPI == kPartial ? (int)((int64_t)sp * nk_all / o.splits) : 0;
-    const int nk = EPI == kPartial ? (int)((int64_t)(sp + 1) * nk_all / o.splits) : nk_all;
-    issue(k_begin, 0);
-    for (int kt = k_begin; kt < nk; ++kt) {
-        const int st = (kt - k_begin) & 1;
+    const int nk = o.K / kBK;
+    issue(0, 0);
+    for (int kt = 0; kt < nk; ++kt) {
+        const int st = kt & 1;
         wait_all_copies();   // this wave's copies of step kt landed
         __syncthreads();     // ... and every wave's; step kt-1's stage is free
         if (kt + 1 < nk) issue(kt + 1, st ^ 1);
@@ -226,7 +227,7 @@ __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int ti
     }
 
     // epilogue: acc[nb][mb][i] = y[m0 + wm*WM + mb*16 + x][n0 + wn*16*NB + nb*16 + 4g + i]
-    constexpr bool BF16_OUT = EPI == kBias || EPI == kBiasGelu || EPI == kBiasSilu;
+    constexpr bool BF16_OUT = EPI == kBias || EPI == kBiasGelu;
     if constexpr (BF16_OUT) {
         // A whole-width tile with 16-byte aligned rows goes out as full rows:
         // the values are staged in the (now idle) LDS, row-major with 16-byte
@@ -254,7 +255,7 @@ __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int ti
                     bf16x4 w;
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        w[i] = (__bf16)(EPI == kBiasGelu ? gelu_tanh(y[i]) : EPI == kBiasSilu ? silu(y[i]) : y[i]);
+                        w[i] = (__bf16)(EPI == kBiasGelu ? gelu_tanh(y[i]) : y[i]);
                     *(__attribute__((address_space(3))) bf16x4 *)((lds_char *)smem + r * (BN * 2) +
                                                                  ((c ^ (r & 15)) * 16) + (g & 1) * 8) = w;
                 }
@@ -341,17 +342,14 @@ __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int ti
             const int m = m0 + wm * WM + mb * 16 + x;
             if (m >= o.M) continue;
             const f32x4 y = acc[nb][mb] + bv;
-            if constexpr (EPI == kPartial) {
-                *reinterpret_cast<f32x4 *>(static_cast<float *>(o.out) + ((int64_t)sp * o.M + m) * o.ldo + n) =
-                    acc[nb][mb];
-            } else if constexpr (EPI == kGatedRes) {
+            if constexpr (EPI == kGatedRes) {
                 f32x4 *p = reinterpret_cast<f32x4 *>(static_cast<float *>(o.out) + (int64_t)m * o.ldo + n);
                 *p = *p + gv * y;
             } else {
                 bf16x4 w;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    w[i] = (__bf16)(EPI == kBiasGelu ? gelu_tanh(y[i]) : EPI == kBiasSilu ? silu(y[i]) : y[i]);
+                    w[i] = (__bf16)(EPI == kBiasGelu ? gelu_tanh(y[i]) : y[i]);
                 *reinterpret_cast<bf16x4 *>(static_cast<uint16_t *>(o.out) + (int64_t)m * o.ldo + n) = w;
             }
         }
@@ -455,27 +453,38 @@ struct Dense {
         }
         return q;
     }
-    __device__ void copy(const Row &q, int kt, uint32_t lds) const
+    // what the copies of K step kt share (wave-uniform)
+    struct Step {
+        const char *base;
+    };
+    __device__ Step at(int kt) const
+    {
+        const int64_t k = (int64_t)kt * kRowBytes;
+        if constexpr (WIDE)
+            return Step{reinterpret_cast<const char *>(k)};
+        else
+            return Step{reinterpret_cast<const char *>(p + (int64_t)r0 * ld) + k};
+    }
+    // a row's copy at a step: its address (vector work, done a few MFMAs ahead), and the copy
+    struct Addr {
+        const char *ptr;
+        uint32_t off;
+    };
+    __device__ Addr addr(const Row &q, const Step &s) const
     {
         if constexpr (WIDE)
-            lds_copy16_v(q.ptr + (int64_t)kt * kRowBytes, lds);
+            return Addr{q.ptr + reinterpret_cast<int64_t>(s.base), 0};
         else
-            lds_copy16_s(reinterpret_cast<const char *>(p + (int64_t)r0 * ld) + (int64_t)kt * kRowBytes, q.off, lds);
+            return Addr{s.base, q.off};
+    }
+    __device__ void copy(const Addr &a, uint32_t lds) const
+    {
+        if constexpr (WIDE)
+            lds_copy16_v(a.ptr, lds);
+        else
+            lds_copy16_s(a.ptr, a.off, lds);
     }
 };
-
-// Tile (row block, channel block) of workgroup bid among n_tiles: the
-// XCD-aware order of tile_body.
-__device__ __forceinline__ void tile_of(int bid, int tiles_n, int n_tiles, int &tm, int &tn)
-{
-    const int xcd = bid & 7, slot = bid >> 3;
-    const int tile = xcd * (n_tiles >> 3) + min(xcd, n_tiles & 7) + slot;
-    const int tiles_m = n_tiles / tiles_n;
-    const int group = tile / (kGroupM * tiles_n), in_group = tile - group * kGroupM * tiles_n;
-    const int gm = min(tiles_m - group * kGroupM, kGroupM);
-    tm = group * kGroupM + in_group % gm;
-    tn = in_group / gm;
-}
 
 // c += a b.  Tiles with one wave per SIMD keep up to 256 accumulation
 // registers: written as an instruction whose result is tied to its addend,
@@ -524,8 +533,10 @@ __device__ __forceinline__ void mma4(const ASrc &as, const WSrc &ws, int k0, int
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char *)smem;
     const uint32_t la0 = __builtin_amdgcn_readfirstlane(lds0 + wave * AP * 1024);
     const uint32_t lw0 = __builtin_amdgcn_readfirstlane(lds0 + wave * WP * 1024);
-    auto copy_a = [&](int i, uint32_t so, int kt) { as.copy(arow[i], kt, la0 + so + i * 1024); };
-    auto copy_w = [&](int i, uint32_t so, int kt) { ws.copy(wrow[i], kt, lw0 + so + i * 1024); };
+    auto copy_a = [&](const typename ASrc::Addr &ad, int i, uint32_t so) { as.copy(ad, la0 + so + i * 1024); };
+    auto copy_w = [&](int i, uint32_t so, const typename WSrc::Step &st) {
+        ws.copy(ws.addr(wrow[i], st), lw0 + so + i * 1024);
+    };
 
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
@@ -549,13 +560,14 @@ __device__ __forceinline__ void mma4(const ASrc &as, const WSrc &ws, int k0, int
 
     const int kl = k1 - 1;
 #pragma unroll
-    for (int i = 0; i < AP; ++i) copy_a(i, 0, k0);
+    for (int s = 0; s < 2; ++s) {
+        const auto sa = as.at(min(k0 + s, kl));
+        const auto sw = ws.at(min(k0 + s, kl));
 #pragma unroll
-    for (int i = 0; i < WP; ++i) copy_w(i, W0, k0);
+        for (int i = 0; i < AP; ++i) copy_a(as.addr(arow[i], sa), i, s * AB);
 #pragma unroll
-    for (int i = 0; i < AP; ++i) copy_a(i, AB, min(k0 + 1, kl));
-#pragma unroll
-    for (int i = 0; i < WP; ++i) copy_w(i, W0 + WB, min(k0 + 1, kl));
+        for (int i = 0; i < WP; ++i) copy_w(i, W0 + s * WB, sw);
+    }
     __asm__ volatile("s_waitcnt vmcnt(%0)" : : "n"(AP + WP) : "memory");
     __builtin_amdgcn_s_barrier();
     __asm__ volatile("" : : : "memory");
@@ -565,9 +577,11 @@ __device__ __forceinline__ void mma4(const ASrc &as, const WSrc &ws, int k0, int
     constexpr int RD = NM * 3 / 4;  // a half's reads are spread over this many MFMAs
     uint32_t ao = 0, wo = W0;
     for (int kt = k0; kt < k1; ++kt) {
-        const int k2 = min(kt + 2, kl);
+        const auto sa = as.at(min(kt + 2, kl));
+        const auto sw = ws.at(min(kt + 2, kl));
         const uint32_t ao1 = ao + AB == AS * AB ? 0 : ao + AB, wo1 = wo == W0 ? W0 + WB : W0;
         const uint32_t ao2 = ao1 + AB == AS * AB ? 0 : ao1 + AB;
+        typename ASrc::Addr ad{};
         // first half; with three A stages, A of step kt + 2 goes where step
         // kt - 1's was (its last read lies before the previous barrier)
 #pragma unroll
@@ -576,9 +590,17 @@ __device__ __forceinline__ void mma4(const ASrc &as, const WSrc &ws, int k0, int
             for (int f = 0; f < NF; ++f)
                 if (f * RD / NF / 2 * 2 == i) rd(ao, wo, 1, f);
             if constexpr (AS == 3) {
+                // a copy's address is formed two MFMAs before the copy
 #pragma unroll
-                for (int l = 0; l < AP; ++l)
-                    if ((l * NM / AP + 2) / 2 * 2 == i) copy_a(l, ao2, k2);
+                for (int l = 0; l < AP; ++l) {
+                    const int at = (l * NM / AP + 2) / 2 * 2;
+                    if (at == i) copy_a(ad, l, ao2);
+                }
+#pragma unroll
+                for (int l = 0; l < AP; ++l) {
+                    const int at = (l * NM / AP + 2) / 2 * 2;
+                    if (at == i + 2) ad = as.addr(arow[l], sa);
+                }
             }
             mfma2(0, i);
             __builtin_amdgcn_sched_barrier(0);
@@ -598,9 +620,9 @@ __device__ __forceinline__ void mma4(const ASrc &as, const WSrc &ws, int k0, int
             for (int l = 0; l < NC; ++l)
                 if (l * RD / NC / 2 * 2 == i) {
                     if (AS == 3 || l >= AP)
-                        copy_w(AS == 3 ? l : l - AP, wo, k2);
+                        copy_w(AS == 3 ? l : l - AP, wo, sw);
                     else
-                        copy_a(l, ao, k2);
+                        copy_a(as.addr(arow[l], sa), l, ao);
                 }
             mfma2(1, i);
             __builtin_amdgcn_sched_barrier(0);
@@ -613,6 +635,26 @@ __device__ __forceinline__ void mma4(const ASrc &as, const WSrc &ws, int k0, int
         __builtin_amdgcn_sched_barrier(0);
     }
     wait_all_copies();
+}
+
+// An accumulator's value for the epilogue, by explicit moves where mfma_into
+// is an instruction of its own: no other code then touches those registers,
+// so that none can be placed (a copy, a spill) between the last MFMAs and the
+// wait states that end mma4.  build.py refuses a build in which one of these
+// kernels spills.
+template <class S>
+__device__ __forceinline__ f32x4 acc_value(f32x4 &a)
+{
+    if constexpr (S::WPE == 1) {
+        f32x4 v;
+        __asm__ volatile("v_accvgpr_read_b32 %0, %4\n\tv_accvgpr_read_b32 %1, %5\n\t"
+                         "v_accvgpr_read_b32 %2, %6\n\tv_accvgpr_read_b32 %3, %7"
+                         : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+                         : "a"(a[0]), "a"(a[1]), "a"(a[2]), "a"(a[3]));
+        return v;
+    } else {
+        return a;
+    }
 }
 
 // Activation of an epilogue.
@@ -659,7 +701,7 @@ __device__ __forceinline__ void store4(const Out &o, int m0, int n0, int sp, cha
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb) {
                     const int r = wm * 16 * MB + mb * 16 + x;
-                    const f32x4 y = acc[nb][mb] + bv;
+                    const f32x4 y = acc_value<S>(acc[nb][mb]) + bv;
                     bf16x4 w;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) w[i] = (__bf16)activate<EPI>(y[i]);
@@ -699,7 +741,7 @@ __device__ __forceinline__ void store4(const Out &o, int m0, int n0, int sp, cha
                         for (int mb = 0; mb < MB; ++mb) {
                             const int r = wm * 16 * MB + mb * 16 + x;
                             *(__attribute__((address_space(3))) f32x4 *)((lds_char *)smem + r * (HALF * 4) +
-                                                                        ((c ^ (r & 7)) * 16)) = acc[nb][mb] + bv;
+                                                                        ((c ^ (r & 7)) * 16)) = acc_value<S>(acc[nb][mb]) + bv;
                         }
                     }
                 }
@@ -743,7 +785,7 @@ __device__ __forceinline__ void store4(const Out &o, int m0, int n0, int sp, cha
         for (int mb = 0; mb < MB; ++mb) {
             const int m = m0 + wm * 16 * MB + mb * 16 + x;
             if (m >= o.M) continue;
-            const f32x4 y = acc[nb][mb] + bv;
+            const f32x4 y = acc_value<S>(acc[nb][mb]) + bv;
             if constexpr (EPI == kPartial) {
                 *reinterpret_cast<f32x4 *>(static_cast<float *>(o.out) + ((int64_t)sp * o.M + m) * o.ldo + n) = y;
             } else if constexpr (EPI == kGatedRes) {

@@ -2,7 +2,7 @@
 // causal 3D convolutions of a VAE stage run on each tile's region (its core
 // widened by a halo), and the blended gather of the tiles into the plane.
 //
-// Convolution as an implicit GEMM on the shared bf16 MFMA tile kernel
+// Convolution as an implicit GEMM on the four-wave MFMA tile kernel
 // (gemm_tile.hpp): rows are the output pixels (tile, frame, row, column) of
 // the listed tiles, K runs over the 27 taps x Cin channels, and the weights
 // [Cout, 3, 3, 3, Cin] are K-contiguous per output channel -- the linear
@@ -10,10 +10,10 @@
 // contiguous run of Cin values, so a K step of 64 channels of one tap is
 // one 128-byte row per pixel, copied HBM -> LDS like a dense row; a tap
 // that falls before the first frame or outside the tile's region is copied
-// from a page of zeros instead (the zero padding).  Tiles of 128 pixel
-// rows x 384 output channels; when they are too few to fill the compute
-// units (one GPU's single tile), K is split into ranges whose f32 partial
-// sums a second kernel adds, with the bias and the activation.
+// from a page of zeros instead (the zero padding).  Where the output tiles are
+// too few to fill the compute units (one GPU's single tile), K is split into
+// ranges whose f32 partial sums a second kernel adds, with the bias and the
+// activation.
 //
 // Blend: one thread per (pixel, 8 channels) walks the tiles whose region
 // covers the pixel and adds weight x value, the weight the product of the
@@ -24,7 +24,9 @@
 
 #include <algorithm>
 
+#include "attn_kernels.hpp"
 #include "gemm_tile.hpp"
+#include "tile_plan.hpp"
 
 // 128 bytes of zeros in device memory: the source of the copies that stand
 // for padding taps (read only).
@@ -34,76 +36,145 @@ namespace regenvc {
 namespace {
 
 using tile::kBK;
-using tile::kThreads;
 
-// Output tile of the convolution: 128 rows x 384 channels (all of Cout up to
-// 384: each gathered A row block is read once for every output channel);
-// waves 2 x 4, each 64 rows x 96 channels.
-constexpr int kConvBM = 128;
-constexpr int kConvNB = 6;
-constexpr int kConvBN = 16 * kConvNB * 4;
 typedef tile::bf16x8 bf16x8;
 typedef tile::f32x4 f32x4;
 
-// A rows of the convolution: pixel m of the listed tiles' regions, K step kt
-// = tap kt / (Cin / 64), channels 64 (kt % (Cin / 64)) .. +63.  A row keeps
-// the address of its own pixel (the centre tap of the current frame) and
-// its position and region size; everything that depends on the tap is
-// wave-uniform (scalar): the tap's offset from the row's address and which
-// bounds it can cross.
-struct ConvA {
-    const uint16_t *in;
-    const ConvArgs *a;
-    int cpt;              // K steps per tap
-    int64_t frame_px;     // pixels per frame of the input (plane, or a tile buffer)
-    int64_t row_px;       // pixels per row of the input
-    struct Row {
-        const uint16_t *base;
-        int t, y, x, h, w;
-    };
-    __device__ Row row(int m, int chunk) const
+typedef tile::Shape4<8, 8, 3, 1> Tile256x256;
+typedef tile::Shape4<8, 6, 3, 1> Tile256x192;
+typedef tile::Shape4<6, 6, 3, 1> Tile192x192;
+typedef tile::Shape4<4, 4, 3, 2> Tile128x128;
+
+enum ConvTile : int32_t { kConv256x256, kConv256x192, kConv192x192, kConv128x128 };
+
+// n / d and n % d for n < 2^31 with inv = min(2^32 / d, 2^32 - 1): the
+// estimate is at most one too small.
+__device__ __forceinline__ int div_by(int n, int d, uint32_t inv, int &rem)
+{
+    int q = (int)__umulhi((uint32_t)n, inv);
+    rem = n - q * d;
+    if (rem >= d) rem -= d, ++q;
+    return q;
+}
+
+// K of the convolution runs over the channels in blocks of 64 and, within a
+// block, over the 27 taps: K step kt = channels 64 (kt / 27) .. +63 of tap
+// kt % 27.  A pixel's 128 bytes of a block are then read again by the
+// neighbouring taps one, three and nine steps later, while they are still in
+// the XCD's L2 (the 32 tiles of an XCD read 1 MB of pixels a step); with the
+// taps outermost they came from beyond it.
+constexpr int kTaps = 27;
+
+// Weight rows [27, Cin] in that order.
+template <bool WIDE>
+struct ConvW : tile::Dense<WIDE> {
+    int Cin;
+    typedef typename tile::Dense<WIDE>::Step Step;
+    __device__ Step at(int kt) const
     {
-        Row r;
-        r.x = m % a->Wr;
-        int q = m / a->Wr;
-        r.y = q % a->Hr;
-        q /= a->Hr;
-        r.t = q % a->T;
-        const int ti = q / a->T;
-        const VaeTile &tl = a->tiles[ti];
-        r.h = tl.reg_y1 - tl.reg_y0;
-        r.w = tl.reg_x1 - tl.reg_x0;
-        int64_t pix;
-        if (a->in_is_plane)
-            pix = ((int64_t)r.t * a->H + tl.reg_y0 + r.y) * a->W + tl.reg_x0 + r.x;
-        else
-            pix = ((int64_t)ti * a->T + r.t) * frame_px + (int64_t)r.y * a->Wr + r.x;
-        r.base = in + pix * a->Cin + chunk * 8;
-        return r;
-    }
-    __device__ const uint16_t *src(const Row &r, int kt) const
-    {
-        const int tap = kt / cpt, c0 = (kt - tap * cpt) * kBK;  // wave-uniform
-        const int dt = tap / 9 - 2, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-        const int64_t off = ((int64_t)dt * frame_px + (int64_t)dy * row_px + dx) * a->Cin + c0;
-        const bool ok = r.t + dt >= 0 && (unsigned)(r.y + dy) < (unsigned)r.h && (unsigned)(r.x + dx) < (unsigned)r.w;
-        return ok ? r.base + off : vae_zero_page;
+        const int c = (int)((uint32_t)kt / kTaps), tap = kt - c * kTaps;
+        Step s = tile::Dense<WIDE>::at(c);
+        s.base += (int64_t)tap * (Cin * 2);
+        return s;
     }
 };
 
-// EPI == kPartial: split-K, f32 partial sums of `splits` K ranges into the
-// workspace (bias and activation follow in vae_reduce_kernel).
-template <int BM, int EPI>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// A rows of the convolution: pixel m of the listed tiles' regions.  A row keeps
+// the address of its own pixel (the centre tap of the current frame) and one
+// bit per tap that is set where the tap lies inside the region; what depends
+// on the tap alone is wave-uniform (scalar).  A copy then costs a select
+// between the tap's address and the page of zeros, without a branch.
+struct ConvSrc {
+    const ConvArgs *a;
+    int m0, rows;
+    struct Row {
+        const char *ptr;
+        uint32_t ok;
+    };
+    __device__ Row row(int r, int chunk) const
+    {
+        int x, y, t;
+        const int m = min(m0 + r, rows - 1);
+        int q = div_by(m, a->Wr, a->inv_w, x);
+        q = div_by(q, a->Hr, a->inv_h, y);
+        const int ti = div_by(q, a->T, a->inv_t, t);
+        const VaeTile &tl = a->tiles[ti];
+        const int h = tl.reg_y1 - tl.reg_y0, w = tl.reg_x1 - tl.reg_x0;
+        int64_t pix;
+        if (a->in_is_plane)
+            pix = ((int64_t)t * a->H + tl.reg_y0 + y) * a->W + tl.reg_x0 + x;
+        else
+            pix = (((int64_t)ti * a->T + t) * a->Hr + y) * a->Wr + x;
+        Row o;
+        o.ptr = static_cast<const char *>(a->in) + pix * a->Cin * 2 + chunk * 16;
+        // taps dx = -1, 0, 1 as bits 0..2, then three rows of them, then three frames
+        uint32_t bx = 0, by = 0;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            if ((unsigned)(x + d - 1) < (unsigned)w) bx |= 1u << d;
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            if ((unsigned)(y + d - 1) < (unsigned)h) by |= bx << (3 * d);
+        }
+        o.ok = by << 18;
+        if (t >= 1) o.ok |= by << 9;
+        if (t >= 2) o.ok |= by;
+        return o;
+    }
+    // the tap of K step kt: its offset from a row's own pixel and its bit (the
+    // three taps of a kernel row are neighbours in memory, with a jump from one
+    // kernel row to the next and another from one frame to the next)
+    struct Step {
+        uint32_t lo, hi, bit;
+    };
+    __device__ Step at(int kt) const
+    {
+        const uint32_t c = (uint32_t)kt / kTaps, tap = (uint32_t)kt - c * kTaps, kr = tap / 3, kf = tap / 9;
+        const int64_t off = a->tap0 + (int64_t)tap * (a->Cin * 2) + (int64_t)kr * a->row_jump +
+                            (int64_t)kf * a->frame_jump + (int64_t)c * tile::kRowBytes;
+        // in scalar registers: the copies' selects are then all that is left to the vector unit
+        return Step{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)off),
+                    (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)off >> 32)),
+                    (uint32_t)__builtin_amdgcn_readfirstlane(1u << tap)};
+    }
+    struct Addr {
+        const void *ptr;
+    };
+    __device__ Addr addr(const Row &r, const Step &s) const
+    {
+        const uint64_t p = reinterpret_cast<uint64_t>(r.ptr) + (((uint64_t)s.hi << 32) | s.lo);
+        const uint64_t z = reinterpret_cast<uint64_t>(static_cast<const void *>(vae_zero_page));
+        const bool ok = (r.ok & s.bit) != 0;
+        const uint32_t lo = ok ? (uint32_t)p : (uint32_t)z, hi = ok ? (uint32_t)(p >> 32) : (uint32_t)(z >> 32);
+        return Addr{reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo)};
+    }
+    __device__ void copy(const Addr &ad, uint32_t lds) const { tile::lds_copy16_v(ad.ptr, lds); }
+};
+
+// One tile of shape S per workgroup.  EPI == kPartial: split-K, f32 partial
+// sums of `splits` K ranges into the workspace (bias and activation follow in
+// vae_reduce_kernel).
+template <class S, int EPI, bool WIDE>
+__global__ __launch_bounds__(tile::kThreads4) __attribute__((amdgpu_waves_per_eu(S::WPE, S::WPE)))
 void conv3d_kernel(ConvArgs a, int tiles_n, int n_tiles, int splits)
 {
-    __shared__ __attribute__((aligned(1024))) char smem[tile::lds_bytes<BM, 4, kConvNB>()];
-    const ConvA src{static_cast<const uint16_t *>(a.in), &a, a.Cin / kBK,
-                    a.in_is_plane ? (int64_t)a.H * a.W : (int64_t)a.Hr * a.Wr, a.in_is_plane ? a.W : a.Wr};
-    const bool part = EPI == tile::kPartial;
-    const tile::Out o{static_cast<const uint16_t *>(a.w), part ? nullptr : static_cast<const uint16_t *>(a.bias),
-                      nullptr, part ? a.ws : a.out, a.Cout, a.n_tiles * a.T * a.Hr * a.Wr, a.Cout, 27 * a.Cin, splits};
-    tile::tile_body<BM, 4, EPI, ConvA, kConvNB>(src, o, tiles_n, n_tiles, smem);
+    __shared__ __attribute__((aligned(1024))) char smem[S::LDS];
+    constexpr bool PART = EPI == tile::kPartial;
+    const int sp = PART ? (int)blockIdx.x / n_tiles : 0;
+    int tm, tn;
+    tile::tile_of((int)blockIdx.x - sp * n_tiles, tiles_n, n_tiles, tm, tn);
+    const int m0 = tm * S::BM, n0 = tn * S::BN;
+    const int nk = kTaps * (a.Cin / kBK), M = a.n_tiles * a.T * a.Hr * a.Wr;
+    const int k0 = PART ? (int)((int64_t)sp * nk / splits) : 0;
+    const int k1 = PART ? (int)((int64_t)(sp + 1) * nk / splits) : nk;
+    const ConvSrc as{&a, m0, M};
+    const ConvW<WIDE> ws{{static_cast<const uint16_t *>(a.w), (int64_t)kTaps * a.Cin, a.Cout, n0}, a.Cin};
+    f32x4 acc[S::NB][S::MB];
+    tile::mma4<S>(as, ws, k0, k1, smem, acc);
+    const tile::Out o{nullptr, static_cast<const uint16_t *>(a.bias), nullptr, PART ? a.ws : a.out, a.Cout, M, a.Cout,
+                      27 * a.Cin, splits};
+    tile::store4<S, EPI>(o, m0, n0, sp, smem, acc);
 }
 
 // Sum of the split-K partials, bias and activation: one thread per 8
@@ -173,72 +244,79 @@ __global__ __launch_bounds__(256) void vae_blend_kernel(BlendArgs a)
     *reinterpret_cast<bf16x8 *>(static_cast<uint16_t *>(a.out) + (((int64_t)t * a.H + y) * a.W + x) * a.C + c) = o;
 }
 
+template <class S, bool WIDE = false>
 hipError_t launch_conv(const ConvArgs &a, int splits, hipStream_t stream)
 {
-    constexpr int BM = kConvBM;
     const int64_t M = (int64_t)a.n_tiles * a.T * a.Hr * a.Wr;
-    const int tiles_n = tile::tiles_along(a.Cout, kConvBN);
-    const int n_tiles = (int)((M + BM - 1) / BM) * tiles_n;
+    const int tiles_n = tile::tiles_along(a.Cout, S::BN);
+    const int n_tiles = (int)((M + S::BM - 1) / S::BM) * tiles_n;
+    const dim3 grid((unsigned)n_tiles * (unsigned)splits), block(tile::kThreads4);
     if (splits > 1) {
-        hipLaunchKernelGGL((conv3d_kernel<BM, tile::kPartial>), dim3((unsigned)(n_tiles * splits)), dim3(kThreads), 0,
-                           stream, a, tiles_n, n_tiles, splits);
+        hipLaunchKernelGGL((conv3d_kernel<S, tile::kPartial, WIDE>), grid, block, 0, stream, a, tiles_n, n_tiles, splits);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         const int64_t n = M * (a.Cout / 8);
-        const dim3 grid((unsigned)((n + 255) / 256));
+        const dim3 rgrid((unsigned)((n + 255) / 256));
         if (a.silu)
-            hipLaunchKernelGGL(vae_reduce_kernel<true>, grid, dim3(256), 0, stream, a, splits);
+            hipLaunchKernelGGL(vae_reduce_kernel<true>, rgrid, dim3(256), 0, stream, a, splits);
         else
-            hipLaunchKernelGGL(vae_reduce_kernel<false>, grid, dim3(256), 0, stream, a, splits);
+            hipLaunchKernelGGL(vae_reduce_kernel<false>, rgrid, dim3(256), 0, stream, a, splits);
     } else if (a.silu) {
-        hipLaunchKernelGGL((conv3d_kernel<BM, tile::kBiasSilu>), dim3((unsigned)n_tiles), dim3(kThreads), 0, stream,
-                           a, tiles_n, n_tiles, 1);
+        hipLaunchKernelGGL((conv3d_kernel<S, tile::kBiasSilu, WIDE>), grid, block, 0, stream, a, tiles_n, n_tiles, 1);
     } else {
-        hipLaunchKernelGGL((conv3d_kernel<BM, tile::kBias>), dim3((unsigned)n_tiles), dim3(kThreads), 0, stream, a,
-                           tiles_n, n_tiles, 1);
+        hipLaunchKernelGGL((conv3d_kernel<S, tile::kBias, WIDE>), grid, block, 0, stream, a, tiles_n, n_tiles, 1);
     }
     return hipGetLastError();
 }
 
-int cu_count_here()
-{
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 256;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
-    return n;
-}
-
 }  // namespace
 
-// Split-K when the output tiles (128 rows x all channels) leave more than
-// half the compute units idle: K (27 taps x Cin) cut into as many ranges as
-// fill the CUs in one round (at most 8), limited by the workspace (one f32
-// copy of the output per range).  One split VAE tile of the window (8092
-// pixels: 64 row tiles) runs as 64 x 4 workgroups.
-int conv_splits(int64_t M, int N, int Cin, int n_cu, int64_t ws_bytes)
+// The tile and K split of a convolution, by plan_tiles; the constants are
+// fitted to 14 shapes of 768 to 64736 pixels and 128 to 384 channels (the
+// choice is on average 0.2 % slower than the best of all tiles and splits of
+// at most 8 ranges).  64736 pixels x 384 channels: 430 -> 393 us a
+// convolution (256 x 192, 506 tiles: two rounds), one tile of the split plane
+// (8092 pixels) 72.7 -> 72.5 us (256 x 192 in four ranges), 3468 pixels
+// x 384 channels 38.3 us (128 x 128 in three).  A step costs a fifth more than
+// a linear layer's: its pixel addresses are selected in vector registers.
+TilePlan conv_plan(int64_t M, int N, int Cin, int n_cu, int64_t ws_bytes)
 {
-    const int64_t tiles = (M + kConvBM - 1) / kConvBM * ((N + kConvBN - 1) / kConvBN);
-    const int nk = 27 * Cin / kBK;
-    if (tiles * 2 > n_cu) return 1;
-    int s = (int)std::min<int64_t>(8, n_cu / tiles);
-    s = std::min(s, nk);
-    const int64_t plane = M * N * (int64_t)sizeof(float);
-    if (plane > 0) s = (int)std::min<int64_t>(s, ws_bytes / plane);
-    return s >= 2 ? s : 1;
+    static const TileCost kCosts[] = {
+        {kConv256x256, 256, 256, 15.0, 15.0, 1.20, 1.15, true},
+        {kConv256x192, 256, 192, 12.2, 12.2, 0.947, 1.15, true},
+        {kConv192x192, 192, 192, 10.9, 10.9, 0.75, 1.15, true},
+        {kConv128x128, 128, 128, 2.0, 2.0, 0.45, 1.05, true},
+    };
+    return plan_tiles(kCosts, SplitCost{3.0, 7.0e6, 2}, M, N, kTaps * (Cin / kBK), n_cu, ws_bytes);
 }
 
 size_t conv_workspace_bytes(int64_t M, int N, int Cin, int n_cu)
 {
-    const int s = conv_splits(M, N, Cin, n_cu, INT64_MAX);
+    const int s = conv_plan(M, N, Cin, n_cu, INT64_MAX).splits;
     return s > 1 ? (size_t)s * M * N * sizeof(float) : 0;
 }
 
-hipError_t launch_vae_conv(const ConvArgs &a, hipStream_t stream)
+hipError_t launch_vae_conv(const ConvArgs &args, hipStream_t stream)
 {
-    const int64_t M = (int64_t)a.n_tiles * a.T * a.Hr * a.Wr;
+    const int64_t M = (int64_t)args.n_tiles * args.T * args.Hr * args.Wr;
     if (M == 0) return hipSuccess;
-    const int splits = a.ws != nullptr ? conv_splits(M, a.Cout, a.Cin, cu_count_here(), a.ws_bytes) : 1;
-    return launch_conv(a, splits, stream);
+    ConvArgs a = args;
+    auto inv = [](int d) { return (uint32_t)std::min<uint64_t>((1ull << 32) / (uint32_t)d, 0xffffffffu); };
+    a.inv_w = inv(a.Wr), a.inv_h = inv(a.Hr), a.inv_t = inv(a.T);
+    const int64_t px = (int64_t)a.Cin * 2, row = (a.in_is_plane ? a.W : a.Wr) * px;
+    const int64_t frame = (a.in_is_plane ? a.H : a.Hr) * row;
+    a.tap0 = -2 * frame - row - px;  // tap (-2, -1, -1)
+    a.row_jump = row - 3 * px, a.frame_jump = frame - 3 * row;
+    const TilePlan p = conv_plan(M, a.Cout, a.Cin, device_cu_count(), a.ws != nullptr ? a.ws_bytes : 0);
+    // weight rows so long that a tile's offsets may leave 32 bits
+    if ((int64_t)27 * a.Cin >= (1 << 22)) return launch_conv<Tile128x128, true>(a, p.splits, stream);
+    switch (p.tile) {
+    case kConv256x256: return launch_conv<Tile256x256>(a, p.splits, stream);
+    case kConv256x192: return launch_conv<Tile256x192>(a, p.splits, stream);
+    case kConv192x192: return launch_conv<Tile192x192>(a, p.splits, stream);
+    case kConv128x128: return launch_conv<Tile128x128>(a, p.splits, stream);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_vae_blend(const BlendArgs &a, hipStream_t stream)

@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "tile_plan.hpp"
+
 namespace regenvc {
 
 constexpr int kVaeMaxTiles = 16;
@@ -31,9 +33,14 @@ struct ConvArgs {
     VaeTile tiles[kVaeMaxTiles];
     void *ws;          // split-K partials (f32), or null: no split
     int64_t ws_bytes;
+    // filled by launch_vae_conv: 2^32 / Wr, Hr and T; bytes from a pixel to its first tap, from the end of a kernel
+    // row's taps to the next row's, and from the end of a frame's to the next frame's
+    uint32_t inv_w, inv_h, inv_t;
+    int64_t tap0, row_jump, frame_jump;
 };
-// K ranges a launch of M output rows uses with ws_bytes of workspace (1: none).
-int conv_splits(int64_t M, int N, int Cin, int n_cu, int64_t ws_bytes);
+// The tile (output pixels x channels per workgroup) and the number of K
+// ranges (1: none) of a launch of M output rows with ws_bytes of workspace.
+TilePlan conv_plan(int64_t M, int N, int Cin, int n_cu, int64_t ws_bytes);
 // Workspace bytes that give a launch its full split (0: it does not split).
 size_t conv_workspace_bytes(int64_t M, int N, int Cin, int n_cu);
 hipError_t launch_vae_conv(const ConvArgs &a, hipStream_t stream);

@@ -173,6 +173,39 @@ def test_split_k_every_range_count():
             check_bound(f"split-K {ranges} ranges, tile {i}", g[i, :, :r1 - r0, :c1 - c0], ref, tol)
 
 
+# a shape or more per tile of the plan, whole and split, with ragged last rows
+# and channels
+@pytest.mark.parametrize("T,H,W,Cin,Cout", [(1, 17, 19, 64, 64), (2, 97, 101, 64, 64),     # 128 x 128, split and whole
+                                            (7, 75, 67, 64, 192), (2, 47, 61, 256, 320),   # 192 x 192, whole and split
+                                            (7, 83, 93, 64, 192), (5, 71, 73, 256, 192),   # 256 x 192, whole and split
+                                            (7, 90, 101, 128, 256), (5, 61, 59, 256, 256)])  # 256 x 256, whole and split
+def test_conv_tiles(T, H, W, Cin, Cout):
+    """One region, the whole plane: against the same sums in float64 (one
+    matrix product per tap), each element within one rounding of its value
+    and 2^-19 of the sum of magnitudes."""
+    g = torch.Generator(device="cuda").manual_seed(T * H + Cin)
+    x = torch.randn(T, H, W, Cin, generator=g, device="cuda").bfloat16()
+    w = (torch.randn(Cout, 3, 3, 3, Cin, generator=g, device="cuda") / (27 * Cin) ** 0.5).bfloat16()
+    b = (torch.randn(Cout, generator=g, device="cuda") * 0.02).bfloat16()
+    tiles, Hr, Wr = kern().split(H, W, 1, 1, 0)
+    got = kern().conv3d(x, w, b, list(tiles), Hr, Wr)[0].double()
+
+    def taps(x, w, b):
+        p = torch.nn.functional.pad(x, (0, 0, 1, 1, 1, 1, 2, 0))
+        out = b.expand(T * H * W, -1).clone()
+        for dt in range(3):
+            for dy in range(3):
+                for dx in range(3):
+                    a = p[dt:dt + T, dy:dy + H, dx:dx + W].reshape(T * H * W, Cin)
+                    out += torch.mm(a, w[:, dt, dy, dx].t().contiguous())
+        return out.view(T, H, W, Cout)
+    ref = taps(x.double(), w.double(), b.double())
+    tol = ULP * ref.abs() + 2.0 ** -19 * taps(x.double().abs(), w.double().abs(), b.double().abs())
+    worst = float(((got - ref).abs() / tol).max())
+    print(f"[vae] conv {T}x{H}x{W} {Cin}->{Cout}: max err/bound {worst:.3f}", flush=True)
+    assert worst <= 1.0
+
+
 def test_plain_crop_and_single_tile():
     """band 0 (plain crop to the cores) and a 1 x 1 split (no halo at all: the
     stack on the whole plane) against the oracle."""
