@@ -112,3 +112,14 @@ def test_head_major_input_layout():
     a2 = api().qk_norm_rope(hm(q), hm(k), dev(wq), dev(wk), (2, 6, 10))
     torch.cuda.synchronize()
     assert torch.equal(a1[0], a2[0]) and torch.equal(a1[1], a2[1])
+
+
+@pytest.mark.parametrize("B,S,H,D,grid", [
+    (2, 2100, 3, 64, (5, 20, 21)),    # several tokens per wave, across the batch; one ragged chunk per lane
+    (1, 4201, 5, 128, (7, 21, 29)),   # two chunks per lane, the second ragged; an uneven last token per wave
+    (1, 70, 16, 128, (2, 5, 7)),      # four whole chunks
+    (1, 33, 24, 128, (1, 3, 11)),     # six
+    (1, 33, 64, 128, (1, 3, 11)),     # sixteen, the most
+])
+def test_chunks_and_tokens_per_wave(B, S, H, D, grid):
+    run(f"B={B} S={S} H={H} D={D}", 90 + H + D, B, S, H, D, grid)
