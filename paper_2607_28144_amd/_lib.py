@@ -130,6 +130,17 @@ def load(path: str | None = None) -> ctypes.CDLL:
     return lib
 
 
+def stream_of(device) -> int:
+    """torch's current stream of a device, as the address the C ABI takes.
+    (The raw query where this torch has it: building a Stream object per call
+    costs more than the launch.)"""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is not None and device.index is not None:
+        return raw(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
+
+
 _kept = threading.local()
 
 

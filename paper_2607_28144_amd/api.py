@@ -26,19 +26,35 @@ _DT = {torch.bfloat16: _lib.BF16, torch.float32: _lib.F32}
 def _desc(t: torch.Tensor, name: str, dtype: torch.dtype) -> _lib.Tensor:
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor, got {t.device}")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    if t.dim() != 4:
+    st = t.stride()
+    if len(st) != 4:
         raise ValueError(f"{name} must be [B, S, H, D], got shape {tuple(t.shape)}")
-    if t.numel() > 0 and t.shape[3] > 1 and t.stride(3) != 1:
+    if st[3] != 1 and t.numel() > 0 and t.shape[3] > 1:
         raise ValueError(f"{name}: the head-dim axis must be contiguous")
-    return _lib.Tensor(t.data_ptr(), t.stride(0), t.stride(1), t.stride(2))
+    return _lib.Tensor(t.data_ptr(), st[0], st[1], st[2])
 
 
-def _stream(device: torch.device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+_stream = _lib.stream_of
+
+
+class _Nothing:
+    def __enter__(self):
+        return self
+
+    def __exit__(self, *exc):
+        return False
+
+
+_NOTHING = _Nothing()
+
+
+def _on(device: torch.device):
+    """Context with `device` current (nothing to do where it is already)."""
+    return _NOTHING if torch.cuda.current_device() == device.index else torch.cuda.device(device)
 
 
 def _fptr(t: Optional[torch.Tensor], name: str, shape) -> Optional[int]:
@@ -49,8 +65,16 @@ def _fptr(t: Optional[torch.Tensor], name: str, shape) -> Optional[int]:
     return t.data_ptr()
 
 
+_SCALE = {}   # head dim -> 1/sqrt(D) rounded to float32
+
+
 def _scale(scale: Optional[float], D: int) -> float:
-    return float(torch.tensor(1.0 / math.sqrt(D), dtype=torch.float32)) if scale is None else float(scale)
+    if scale is not None:
+        return float(scale)
+    s = _SCALE.get(D)
+    if s is None:
+        s = _SCALE[D] = float(torch.tensor(1.0 / math.sqrt(D), dtype=torch.float32))
+    return s
 
 
 _NEED = {}    # (device index, shape) -> workspace bytes of the call's plan
@@ -125,7 +149,7 @@ def _attn(fn_name: str, q, k, v, scale, out_dtype, out, want_lse, lse_out):
     lp = _fptr(lse_out, "lse", (B, H, Sq))
     lib = _lib.load()
     need = _workspace_need(q.device, B, H, Sq, Skv, D)
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         if fn_name == "regenvc_attn_partial_fwd":
             st = _with_workspace(q.device, need, lambda: lib.regenvc_attn_partial_fwd(
                 ctypes.byref(qd), ctypes.byref(kd), ctypes.byref(vd), ctypes.byref(od), lp, B, H, Sq, Skv, D,
@@ -205,7 +229,7 @@ def attn_partials_fwd(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, bounds:
     lptrs = (ctypes.c_void_p * n)(*[t.data_ptr() for t in lse_outs])
     lib = _lib.load()
     need = _chunk_plan(q.device, B, H, Sq, [int(x) for x in bounds], D)
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         st = _with_workspace(q.device, need, lambda: lib.regenvc_attn_partials_fwd(
             ctypes.byref(qd), ctypes.byref(kd), ctypes.byref(vd), n, arr, optrs, lptrs, B, H, Sq, Skv, D,
             _scale(scale, D), _stream(q.device)))
@@ -241,7 +265,7 @@ def attn_ring_accumulate(q: torch.Tensor, k_chunk: torch.Tensor, v_chunk: torch.
         od, dt, res = _desc(out, "out", out_dtype), _DT[out_dtype], out
     lib = _lib.load()
     need = _workspace_need(q.device, B, H, Sq, Skv, D)
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         st = _with_workspace(q.device, need, lambda: lib.regenvc_attn_ring_accumulate(
             ctypes.byref(qd), ctypes.byref(kd), ctypes.byref(vd), ctypes.byref(rd), lp,
             ctypes.byref(od) if od is not None else None, dt, B, H, Sq, Skv, D, _scale(scale, D),
@@ -280,7 +304,7 @@ def cross_attn_dual_fwd(q: torch.Tensor, k_txt: torch.Tensor, v_txt: torch.Tenso
     lt, li = _fptr(lse_txt, "lse_txt", (B, H, Sq)), _fptr(lse_img, "lse_img", (B, H, Sq))
     lib = _lib.load()
     need = _workspace_need(q.device, B, H, Sq, St, D, Skv2=Si)
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         st = _with_workspace(q.device, need, lambda: lib.regenvc_cross_attn_dual_fwd(
             ctypes.byref(descs[0]), ctypes.byref(descs[1]), ctypes.byref(descs[2]), St, ctypes.byref(descs[3]),
             ctypes.byref(descs[4]), Si, ctypes.byref(descs[5]), lt, li, B, H, Sq, D, _scale(scale, D),
@@ -316,7 +340,7 @@ def lse_merge(o_parts: Sequence[torch.Tensor], lse_parts: Sequence[torch.Tensor]
     lptrs = (ctypes.c_void_p * n)(*[t.data_ptr() for t in lse_parts])
     lp = _fptr(lse_out, "lse", (B, H, Sq))
     lib = _lib.load()
-    with torch.cuda.device(dev):
+    with _on(dev):
         st = lib.regenvc_lse_merge(optrs, lptrs, n, ctypes.byref(od), _DT[out_dtype], lp, B, H, Sq, D, _stream(dev))
     _lib.check(st, "regenvc_lse_merge")
     return out, lse_out
@@ -360,7 +384,7 @@ def qk_norm_rope(q: torch.Tensor, k: torch.Tensor, w_q: torch.Tensor, w_k: torch
     qo, ko = _desc(q_out, "q_out", torch.bfloat16), _desc(k_out, "k_out", torch.bfloat16)
     gf, gh, gw = (int(x) for x in grid)
     lib = _lib.load()
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         st = lib.regenvc_qk_norm_rope(ctypes.byref(qi), ctypes.byref(ki), w_q.data_ptr(), w_k.data_ptr(),
                                       ctypes.byref(qo), ctypes.byref(ko), B, S, H, D, gf, gh, gw, int(token0),
                                       float(eps), float(theta), _stream(q.device))

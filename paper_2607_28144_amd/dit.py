@@ -18,8 +18,7 @@ from . import _lib
 EPI = {"bias": 0, "bias_gelu": 1, "gated_residual": 2}
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+_stream = _lib.stream_of
 
 
 def _rows(t: torch.Tensor, name: str, dtype: torch.dtype) -> int:

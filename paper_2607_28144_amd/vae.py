@@ -16,8 +16,7 @@ import torch
 from . import _lib
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+_stream = _lib.stream_of
 
 
 def split(H: int, W: int, ty: int, tx: int, halo: int):
