@@ -52,6 +52,7 @@ typedef tile::Shape4<5, 8, 3, 1> Tile160x256;
 typedef tile::Shape4<6, 6, 3, 1> Tile192x192;
 typedef tile::Shape4<4, 4, 3, 2> Tile128x128;
 typedef tile::Shape4<2, 4, 2, 3> Tile64x128;
+typedef tile::Shape4<4, 6, 3, 1> Tile128x192;
 
 // Row strides from which the offsets within a tile (255 rows) may leave 32 bits.
 constexpr int64_t kWideStride = 1 << 22;
@@ -354,27 +355,28 @@ hipError_t launch_linear4(const LinearArgs &a, int splits, hipStream_t stream)
 }  // namespace
 
 // The tile and K split of a linear layer, by plan_tiles; the constants are
-// fitted to 14 row counts from 64 to 10920 of the block's five layers (the
-// choice is on average 1.2 % slower than the best of all tiles and splits).
+// fitted to 11 row counts from 300 to 10920 of the block's five layers (the
+// choice is on average 1.0 % slower than the best of all tiles and splits).
 // Measured, against 256 x 256 or 288 x 256 by eight waves:
-// 1365 x 1536 x 8960 203 -> 49 us (192 x 192 in four ranges),
-// 1560 x 4608 x 1536 39.7 -> 25.0 us (128 x 128), 10920 x 8960 x 1536 with
-// GELU 291 -> 270 us (256 x 256 by four waves); 10920 x 4608 and 10920 x 1536
-// stay with 288 x 256 by eight waves (138 and 46.7 us; the best other tile
-// 143 and 50.2: 228 tiles of 288 rows are one round where 43 row blocks of
-// 256 need 258 tiles).
+// 1365 x 1536 x 8960 203 -> 48 us (192 x 192 in four ranges),
+// 1560 x 4608 x 1536 39.7 -> 24.1 us (128 x 128), 4096 x 1536 x 8960 205 -> 99 us
+// (128 x 192), 10920 x 8960 x 1536 with GELU 286 -> 267 us (256 x 256 by four
+// waves); 10920 x 4608 and 10920 x 1536 stay with 288 x 256 by eight waves
+// (131 and 45.0 us; the best other tile 136 and 48.4: 228 tiles of 288 rows are
+// one round where 43 row blocks of 256 need 258 tiles).
 TilePlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes)
 {
     // fixed times by tile and epilogue
-    static const double kFixed[6][3] = {{8.3, 13.0, 20.0}, {6.2, 9.0, 14.0}, {5.8, 8.2, 13.2},
-                                        {1.0, 2.3, 4.0},   {1.0, 2.0, 2.8},  {5.0, 9.0, 9.0}};
+    static const double kFixed[7][3] = {{5.0, 9.0, 9.0},  {8.3, 13.7, 20.0}, {6.2, 9.0, 14.0}, {5.1, 8.6, 13.2},
+                                        {3.2, 4.5, 8.5},  {1.0, 2.3, 4.0},   {1.0, 2.0, 2.8}};
     const TileCost costs[] = {
-        {kTile288x256, 288, 256, kFixed[5][epi], 0.0, 1.30, 1.32, false},
-        {kTile256x256, 256, 256, kFixed[0][epi], kFixed[0][0], 0.99, 1.32, true},
-        {kTile160x256, 160, 256, kFixed[1][epi], kFixed[1][0], 0.668, 1.32, true},
-        {kTile192x192, 192, 192, kFixed[2][epi], kFixed[2][0], 0.645, 1.32, true},
-        {kTile128x128, 128, 128, kFixed[3][epi], kFixed[3][0], 0.448, 1.02, true},
-        {kTile64x128, 64, 128, kFixed[4][epi], kFixed[4][0], 0.43, 1.02, true},
+        {kTile288x256, 288, 256, kFixed[0][epi], 0.0, 1.274, 1.254, false},
+        {kTile256x256, 256, 256, kFixed[1][epi], kFixed[1][0], 0.99, 1.188, true},
+        {kTile160x256, 160, 256, kFixed[2][epi], kFixed[2][0], 0.668, 1.188, true},
+        {kTile192x192, 192, 192, kFixed[3][epi], kFixed[3][0], 0.645, 1.188, true},
+        {kTile128x192, 128, 192, kFixed[4][epi], kFixed[4][0], 0.52, 1.15, true},
+        {kTile128x128, 128, 128, kFixed[5][epi], kFixed[5][0], 0.448, 0.921, true},
+        {kTile64x128, 64, 128, kFixed[6][epi], kFixed[6][0], 0.43, 1.0, true},
     };
     return plan_tiles(costs, SplitCost{8.5, 5.0e6, epi == kEpiGatedRes ? 8 : 2}, M, N, K / kBK, n_cu, ws_bytes);
 }
@@ -396,6 +398,7 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     case kTile160x256: return launch_linear4<Tile160x256>(a, p.splits, stream);
     case kTile192x192: return launch_linear4<Tile192x192>(a, p.splits, stream);
     case kTile128x128: return launch_linear4<Tile128x128>(a, p.splits, stream);
+    case kTile128x192: return launch_linear4<Tile128x192>(a, p.splits, stream);
     case kTile64x128: return launch_linear4<Tile64x128>(a, p.splits, stream);
     case kTile288x256: return launch_linear_bm<288>(a, stream);
     }

@@ -42,6 +42,7 @@ enum LinearTile : int32_t {
     kTile128x128 = 3,
     kTile64x128 = 4,
     kTile288x256 = 5,
+    kTile128x192 = 6,
 };
 // The plan of this shape on n_cu compute units with ws_bytes of workspace.
 TilePlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes);

@@ -43,9 +43,10 @@ typedef tile::f32x4 f32x4;
 typedef tile::Shape4<8, 8, 3, 1> Tile256x256;
 typedef tile::Shape4<8, 6, 3, 1> Tile256x192;
 typedef tile::Shape4<6, 6, 3, 1> Tile192x192;
+typedef tile::Shape4<4, 6, 3, 1> Tile128x192;
 typedef tile::Shape4<4, 4, 3, 2> Tile128x128;
 
-enum ConvTile : int32_t { kConv256x256, kConv256x192, kConv192x192, kConv128x128 };
+enum ConvTile : int32_t { kConv256x256, kConv256x192, kConv192x192, kConv128x192, kConv128x128 };
 
 // n / d and n % d for n < 2^31 with inv = min(2^32 / d, 2^32 - 1): the
 // estimate is at most one too small.
@@ -122,21 +123,27 @@ struct ConvSrc {
         if (t >= 2) o.ok |= by;
         return o;
     }
-    // the tap of K step kt: its offset from a row's own pixel and its bit (the
-    // three taps of a kernel row are neighbours in memory, with a jump from one
-    // kernel row to the next and another from one frame to the next)
+    // The tap of K step kt: its offset from a row's own pixel and its bit.  Lane
+    // l of tap_lo, tap_hi holds the offset of tap l: read from there, a step's
+    // scalar work is a dozen instructions (forming the offset takes forty, which
+    // one wave per SIMD cannot hide).
     struct Step {
         uint32_t lo, hi, bit;
     };
+    uint32_t tap_lo, tap_hi;
+    __device__ void init()
+    {
+        const int tap = (int)threadIdx.x & 31;
+        const int64_t off = a->tap0 + (int64_t)tap * (a->Cin * 2) + (int64_t)(tap / 3) * a->row_jump +
+                            (int64_t)(tap / 9) * a->frame_jump;
+        tap_lo = (uint32_t)off, tap_hi = (uint32_t)((uint64_t)off >> 32);
+    }
     __device__ Step at(int kt) const
     {
-        const uint32_t c = (uint32_t)kt / kTaps, tap = (uint32_t)kt - c * kTaps, kr = tap / 3, kf = tap / 9;
-        const int64_t off = a->tap0 + (int64_t)tap * (a->Cin * 2) + (int64_t)kr * a->row_jump +
-                            (int64_t)kf * a->frame_jump + (int64_t)c * tile::kRowBytes;
-        // in scalar registers: the copies' selects are then all that is left to the vector unit
-        return Step{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)off),
-                    (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)off >> 32)),
-                    (uint32_t)__builtin_amdgcn_readfirstlane(1u << tap)};
+        const uint32_t c = (uint32_t)kt / kTaps, tap = (uint32_t)kt - c * kTaps;
+        const uint64_t off = (((uint64_t)(uint32_t)__builtin_amdgcn_readlane(tap_hi, tap) << 32) |
+                              (uint32_t)__builtin_amdgcn_readlane(tap_lo, tap)) + (uint64_t)c * tile::kRowBytes;
+        return Step{(uint32_t)off, (uint32_t)(off >> 32), 1u << tap};
     }
     struct Addr {
         const void *ptr;
@@ -168,7 +175,8 @@ void conv3d_kernel(ConvArgs a, int tiles_n, int n_tiles, int splits)
     const int nk = kTaps * (a.Cin / kBK), M = a.n_tiles * a.T * a.Hr * a.Wr;
     const int k0 = PART ? (int)((int64_t)sp * nk / splits) : 0;
     const int k1 = PART ? (int)((int64_t)(sp + 1) * nk / splits) : nk;
-    const ConvSrc as{&a, m0, M};
+    ConvSrc as{&a, m0, M};
+    as.init();
     const ConvW<WIDE> ws{{static_cast<const uint16_t *>(a.w), (int64_t)kTaps * a.Cin, a.Cout, n0}, a.Cin};
     f32x4 acc[S::NB][S::MB];
     tile::mma4<S>(as, ws, k0, k1, smem, acc);
@@ -272,19 +280,20 @@ hipError_t launch_conv(const ConvArgs &a, int splits, hipStream_t stream)
 }  // namespace
 
 // The tile and K split of a convolution, by plan_tiles; the constants are
-// fitted to 14 shapes of 768 to 64736 pixels and 128 to 384 channels (the
-// choice is on average 0.2 % slower than the best of all tiles and splits of
-// at most 8 ranges).  64736 pixels x 384 channels: 430 -> 393 us a
-// convolution (256 x 192, 506 tiles: two rounds), one tile of the split plane
-// (8092 pixels) 72.7 -> 72.5 us (256 x 192 in four ranges), 3468 pixels
-// x 384 channels 38.3 us (128 x 128 in three).  A step costs a fifth more than
-// a linear layer's: its pixel addresses are selected in vector registers.
+// fitted to 23 shapes of 768 to 64736 pixels and 128 to 384 channels.  64736
+// pixels x 384 channels: 430 -> 380 to 393 us a convolution (256 x 192, 506
+// tiles: two rounds), one tile of the split plane (8092 pixels) 72.7 -> 66.9 us
+// (128 x 192 in two ranges; 256 x 192 in four 69.1, its partials twice the
+// bytes), 3468 pixels x 384 channels 37.8 us (128 x 128 in three).  A step costs
+// a fifth more than a linear layer's: its pixel addresses are selected in
+// vector registers.
 TilePlan conv_plan(int64_t M, int N, int Cin, int n_cu, int64_t ws_bytes)
 {
     static const TileCost kCosts[] = {
         {kConv256x256, 256, 256, 15.0, 15.0, 1.20, 1.15, true},
         {kConv256x192, 256, 192, 12.2, 12.2, 0.947, 1.15, true},
         {kConv192x192, 192, 192, 10.9, 10.9, 0.75, 1.15, true},
+        {kConv128x192, 128, 192, 7.6, 7.6, 0.569, 1.15, true},
         {kConv128x128, 128, 128, 2.0, 2.0, 0.45, 1.05, true},
     };
     return plan_tiles(kCosts, SplitCost{3.0, 7.0e6, 2}, M, N, kTaps * (Cin / kBK), n_cu, ws_bytes);
@@ -314,6 +323,7 @@ hipError_t launch_vae_conv(const ConvArgs &args, hipStream_t stream)
     case kConv256x256: return launch_conv<Tile256x256>(a, p.splits, stream);
     case kConv256x192: return launch_conv<Tile256x192>(a, p.splits, stream);
     case kConv192x192: return launch_conv<Tile192x192>(a, p.splits, stream);
+    case kConv128x192: return launch_conv<Tile128x192>(a, p.splits, stream);
     case kConv128x128: return launch_conv<Tile128x128>(a, p.splits, stream);
     }
     return hipErrorInvalidValue;

@@ -106,6 +106,7 @@ def test_linear_epilogues(M, N, K):
                                    (1001, 8960, 1536), (5460, 1552, 1536),                     # 160 x 256
                                    (1365, 8976, 1536),                                         # 256 x 256
                                    (5460, 1536, 1536),                                         # 192 x 192
+                                   (2731, 1552, 1536), (2001, 1536, 8960),                     # 128 x 192, whole and split
                                    (1365, 1552, 8960), (64, 1536, 8960), (700, 1536, 8896)])   # K split
 def test_linear_tiles(M, N, K):
     test_linear_epilogues(M, N, K)

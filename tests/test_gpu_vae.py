@@ -177,7 +177,8 @@ def test_split_k_every_range_count():
 # and channels
 @pytest.mark.parametrize("T,H,W,Cin,Cout", [(1, 17, 19, 64, 64), (2, 97, 101, 64, 64),     # 128 x 128, split and whole
                                             (7, 75, 67, 64, 192), (2, 47, 61, 256, 320),   # 192 x 192, whole and split
-                                            (7, 83, 93, 64, 192), (5, 71, 73, 256, 192),   # 256 x 192, whole and split
+                                            (7, 83, 93, 64, 192), (7, 34, 35, 192, 384),   # 256 x 192 whole, 128 x 192 split
+                                            (5, 71, 73, 256, 192),                         # 128 x 192, whole
                                             (7, 90, 101, 128, 256), (5, 61, 59, 256, 256)])  # 256 x 256, whole and split
 def test_conv_tiles(T, H, W, Cin, Cout):
     """One region, the whole plane: against the same sums in float64 (one
