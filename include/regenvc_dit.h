@@ -116,11 +116,11 @@ typedef struct {
     const void *w_2, *b_2;      /* [C, F], [C]    */
 } regenvc_dit_params;
 
-/* Bytes of workspace regenvc_dit_block_fwd needs for S tokens, S_ctx
+/* Bytes of workspace regenvc_dit_block_fwd can use for S tokens, S_ctx
    context tokens, width C = heads x D, feed-forward F, on a device with
    n_cu compute units: the modulation vectors, the bf16 activations
-   (S x (5 C + F) values) and the attention calls' split-tile scratch.
-   Host-only. */
+   (S x (5 C + F) values) and a scratch that the attention calls' split tiles
+   and the linear layers' partial sums use in turn.  Host-only. */
 regenvc_status regenvc_dit_block_workspace(int32_t S, int32_t S_ctx, int32_t C, int32_t heads, int32_t F,
                                            int32_t n_cu, int64_t *bytes);
 
@@ -130,7 +130,9 @@ regenvc_status regenvc_dit_block_workspace(int32_t S, int32_t S_ctx, int32_t C, 
    precomputed key/values; tokens in (frame, row, column) raster order on a
    grid_f x grid_h x grid_w latent grid from token0 (as
    regenvc_qk_norm_rope).  workspace: device, 256-byte aligned, at least
-   regenvc_dit_block_workspace bytes, not overlapping any other argument.
+   regenvc_dit_block_workspace bytes, not overlapping any other argument (a
+   smaller one is taken down to the attention calls' share of the scratch;
+   the linear layers then cut K into fewer ranges).
    Constraints: S, S_ctx >= 1; D = C / heads in {64, 128}; C a multiple of
    512 (at most 2048); F a multiple of 64.  Allocates nothing. */
 regenvc_status regenvc_dit_block_fwd(float *x, const float *e, const regenvc_dit_params *p,

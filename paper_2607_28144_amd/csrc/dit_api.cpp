@@ -63,9 +63,11 @@ int64_t align256(int64_t b)
     return (b + 255) / 256 * 256;
 }
 
-// Workspace layout of the block forward.
+// Workspace layout of the block forward: `least` bytes hold the activations and
+// the attention calls' split tiles, `total` also the most partial sums that a
+// linear layer can use (between the two its K is cut into fewer ranges).
 struct BlockLayout {
-    int64_t mod, h, qkv, att, f, scr, total;
+    int64_t mod, h, qkv, att, f, scr, least, total;
 };
 
 BlockLayout block_layout(int32_t S, int32_t S_ctx, int32_t C, int32_t heads, int32_t F, int32_t n_cu)
@@ -83,6 +85,7 @@ BlockLayout block_layout(int32_t S, int32_t S_ctx, int32_t C, int32_t heads, int
     if (regenvc::plan_attn(1, heads, S, S, D, n_cu, &p1)) need = (int64_t)regenvc::workspace_bytes(p1, D);
     if (regenvc::plan_attn(1, heads, S, S_ctx, D, n_cu, &p2))
         need = std::max(need, (int64_t)regenvc::workspace_bytes(p2, D));
+    L.least = L.scr + align256(need);
     // the split-K partials of a linear layer use the same scratch: the block's kernels run one after another
     auto linear = [&](int N, int K, int epi) {
         need = std::max(need, (int64_t)regenvc::linear_workspace_bytes(S, N, K, epi, n_cu));
@@ -280,10 +283,11 @@ regenvc_status regenvc_dit_block_fwd(float *x, const float *e, const regenvc_dit
                      (long long)token0 + S - 1, grid_f, grid_h, grid_w);
     if ((st = regenvc::abi::device_ok()) != REGENVC_OK) return st;
     const BlockLayout L = block_layout(S, S_ctx, C, heads, F, regenvc::device_cu_count());
-    if (workspace_bytes < L.total)
+    if (workspace_bytes < L.least)
         return failf(REGENVC_ERR_INVALID_ARG, "%s: workspace of %lld bytes, this call needs %lld", fn,
-                     (long long)workspace_bytes, (long long)L.total);
-    const auto rw = range_of(workspace, L.total);
+                     (long long)workspace_bytes, (long long)L.least);
+    const int64_t used = std::min(workspace_bytes, L.total);
+    const auto rw = range_of(workspace, used);
     if (overlaps(rw, range_of(x, (int64_t)S * C * 4)) || overlaps(rw, range_of(e, (int64_t)C * 4)) ||
         overlaps(rw, range_of(ctx_k, (int64_t)S_ctx * C * 2)) || overlaps(rw, range_of(ctx_v, (int64_t)S_ctx * C * 2)))
         return failf(REGENVC_ERR_INVALID_ARG, "%s: the workspace overlaps another argument", fn);
@@ -292,7 +296,7 @@ regenvc_status regenvc_dit_block_fwd(float *x, const float *e, const regenvc_dit
     char *ws = static_cast<char *>(workspace);
     float *mod = reinterpret_cast<float *>(ws + L.mod);
     void *h = ws + L.h, *qkv = ws + L.qkv, *att = ws + L.att, *f = ws + L.f;
-    const regenvc::Workspace scr{ws + L.scr, (size_t)(L.total - L.scr)};
+    const regenvc::Workspace scr{ws + L.scr, (size_t)(used - L.scr)};
     const int D = C / heads;
     const float scale = (float)(1.0 / std::sqrt((double)D));  // 1/sqrt(D) rounded to float32 once
     hipError_t err = hipSuccess;

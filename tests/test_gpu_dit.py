@@ -281,6 +281,37 @@ def test_block_four_steps_every_row():
         block_errors(f"block step {s + 1}, 336 tokens", dx.cpu().numpy().astype(np.float64), ref, ref2)
 
 
+def test_block_workspace_without_room_for_partial_sums():
+    """A block call is taken from the attention calls' share of the scratch
+    (one byte less is refused) to the queried size, and writes no byte behind
+    what it was given: every row against the oracle at three sizes."""
+    S, S_ctx, C, F, align = 336, 64, 1536, 8960, lambda b: (b + 255) // 256 * 256
+    params = synth.dit_params(11)
+    x, e, kc, vc = synth.dit_inputs(12, S, S_ctx, steps=1)
+    blk = device_block(params)
+    dk, dv, de = dev_bits(kc), dev_bits(vc), torch.from_numpy(e[0]).cuda()
+    from paper_2607_28144_amd import attn_plan
+    n_cu = torch.cuda.get_device_properties(dk.device).multi_processor_count
+    plans = [attn_plan(1, 12, S, n, 128, n_cu) for n in (S, S_ctx)]
+    least = (align(6 * C * 4) + align(S * C * 2) * 2 + align(S * 3 * C * 2) + align(S * F * 2) +
+             align(max(p["workspace_bytes"] for p in plans)))
+    full = blk.workspace_bytes(S, S_ctx, dk.device)
+    assert least < full
+    ref = odit.block(x.astype(np.float64), e[0], params, kc, vc, (7, 6, 8))
+    ref2 = jittered_oracle(1).block(x.astype(np.float64), e[0], params, kc, vc, (7, 6, 8))
+    for size in (least, align((least + full) // 2), full):
+        ws = torch.full((full + 256,), 0x5A, dtype=torch.uint8, device="cuda")
+        blk._ws = {(dk.device.index, S, S_ctx): ws[:size]}
+        dx = torch.from_numpy(x).cuda()
+        blk.forward(dx, de, dk, dv, (7, 6, 8))
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0x5A).all()), "written past the workspace"
+        block_errors(f"block, workspace of {size} bytes", dx.cpu().numpy().astype(np.float64), ref, ref2)
+    blk._ws = {(dk.device.index, S, S_ctx): ws[:least - 1]}
+    with pytest.raises(RuntimeError, match="workspace"):
+        blk.forward(dx, de, dk, dv, (7, 6, 8))
+
+
 def test_block_window_shape_one_step_sampled_rows():
     """The workload's window: 10920 tokens (7 x 30 x 52), 12 heads x 128,
     512 context tokens, one step; sampled rows of the residual stream against
