@@ -127,9 +127,11 @@ def modulation(w_mod: torch.Tensor, b_mod: torch.Tensor, e: torch.Tensor,
 
 class DitBlock:
     """One diffusion-transformer block on the GPU: its bf16 parameters
-    (device tensors, names as in regenvc_dit_params) and a workspace sized
-    per shape, allocated by torch.  forward() runs regenvc_dit_block_fwd,
-    updating the float32 residual stream in place."""
+    (device tensors, names as in regenvc_dit_params).  forward() runs
+    regenvc_dit_block_fwd, updating the float32 residual stream in place, in
+    a workspace of its own from torch's allocator on the current stream:
+    calls from several streams or threads share no memory, and none is held
+    between calls."""
 
     def __init__(self, params: Dict[str, torch.Tensor], heads: int = 12):
         missing = [n for n in _lib.DIT_PARAM_NAMES if n not in params]
@@ -144,7 +146,8 @@ class DitBlock:
             if t.dtype != torch.bfloat16 or t.device.type != "cuda" or not t.is_contiguous():
                 raise ValueError(f"parameter {n} must be a contiguous bf16 device tensor")
         self._c = _lib.DitParams(*[params[n].data_ptr() for n in _lib.DIT_PARAM_NAMES])
-        self._ws = {}
+        self._ws = {}    # (device index, S, S_ctx) -> a workspace for such calls in place of their own
+        self._need = {}  # (device index, S, S_ctx) -> workspace bytes
 
     def workspace_bytes(self, S: int, S_ctx: int, device) -> int:
         n_cu = torch.cuda.get_device_properties(device).multi_processor_count
@@ -152,6 +155,19 @@ class DitBlock:
         st = _lib.load().regenvc_dit_block_workspace(S, S_ctx, self.C, self.heads, self.F, n_cu, ctypes.byref(out))
         _lib.check(st, "regenvc_dit_block_workspace")
         return out.value
+
+    def _workspace(self, S: int, S_ctx: int, device) -> torch.Tensor:
+        key = (device.index, S, S_ctx)
+        ws = self._ws.get(key)
+        if ws is not None:
+            return ws
+        need = self._need.get(key)
+        if need is None:
+            need = self.workspace_bytes(S, S_ctx, device)
+            if len(self._need) >= 4096:
+                self._need.clear()
+            self._need[key] = need
+        return torch.empty(need, dtype=torch.uint8, device=device)
 
     def forward(self, x: torch.Tensor, e: torch.Tensor, ctx_k: torch.Tensor, ctx_v: torch.Tensor, grid,
                 token0: int = 0) -> torch.Tensor:
@@ -165,11 +181,7 @@ class DitBlock:
         for name, t in (("ctx_k", ctx_k), ("ctx_v", ctx_v)):
             if t.dtype != torch.bfloat16 or not t.is_contiguous() or t.numel() != S_ctx * C:
                 raise ValueError(f"{name} must be a contiguous bf16 [S_ctx, heads, D] tensor")
-        key = (x.device.index, S, S_ctx)
-        if key not in self._ws:
-            self._ws[key] = torch.empty(self.workspace_bytes(S, S_ctx, x.device), dtype=torch.uint8,
-                                        device=x.device)
-        ws = self._ws[key]
+        ws = self._workspace(S, S_ctx, x.device)
         gf, gh, gw = (int(v) for v in grid)
         st = _lib.load().regenvc_dit_block_fwd(
             x.data_ptr(), _vec(e, "e", torch.float32, C), ctypes.byref(self._c), ctx_k.data_ptr(), ctx_v.data_ptr(),

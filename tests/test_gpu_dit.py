@@ -328,3 +328,28 @@ def test_block_window_shape_one_step_sampled_rows():
     ref = odit.block(x.astype(np.float64), e[0], params, kc, vc, (7, 30, 52), rows=rows)
     ref2 = jittered_oracle(2).block(x.astype(np.float64), e[0], params, kc, vc, (7, 30, 52), rows=rows)
     block_errors("block window one step (sampled rows)", dx.cpu().numpy().astype(np.float64)[rows], ref, ref2)
+
+
+def test_block_on_two_streams_at_once():
+    """One block, two inputs, each stepped on a stream of its own without
+    waiting for the other: bitwise the outputs of the calls one by one."""
+    S, S_ctx, grid = 336, 64, (7, 6, 8)
+    blk = device_block(synth.dit_params(11))
+    x, e, kc, vc = synth.dit_inputs(12, S, S_ctx, steps=2)
+    dk, dv, de = dev_bits(kc), dev_bits(vc), [torch.from_numpy(v).cuda() for v in e]
+    xs = [torch.from_numpy(x).cuda(), torch.from_numpy(x[::-1].copy()).cuda()]
+    ref = [t.clone() for t in xs]
+    for r in ref:
+        for _ in range(4):
+            for v in de:
+                blk.forward(r, v, dk, dv, grid)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in xs]
+    for _ in range(4):
+        for v in de:
+            for t, s in zip(xs, streams):
+                with torch.cuda.stream(s):
+                    blk.forward(t, v, dk, dv, grid)
+    torch.cuda.synchronize()
+    for t, r in zip(xs, ref):
+        assert torch.equal(t, r)
