@@ -124,15 +124,20 @@ typedef struct {
 regenvc_status regenvc_dit_block_workspace(int32_t S, int32_t S_ctx, int32_t C, int32_t heads, int32_t F,
                                            int32_t n_cu, int64_t *bytes);
 
+/* The fewest bytes that regenvc_dit_block_fwd takes: all of the above with
+   the attention calls' share of the scratch only.  Host-only. */
+regenvc_status regenvc_dit_block_workspace_least(int32_t S, int32_t S_ctx, int32_t C, int32_t heads, int32_t F,
+                                                 int32_t n_cu, int64_t *bytes);
+
 /* One forward of the block over one window: x (f32 [S, C], contiguous) is
    updated in place.  e: f32 [C] conditioning vector of this denoising step;
    ctx_k, ctx_v: bf16 [S_ctx, heads, D] contiguous, the context's
    precomputed key/values; tokens in (frame, row, column) raster order on a
    grid_f x grid_h x grid_w latent grid from token0 (as
    regenvc_qk_norm_rope).  workspace: device, 256-byte aligned, at least
-   regenvc_dit_block_workspace bytes, not overlapping any other argument (a
-   smaller one is taken down to the attention calls' share of the scratch;
-   the linear layers then cut K into fewer ranges).
+   regenvc_dit_block_workspace_least bytes, not overlapping any other argument
+   (below regenvc_dit_block_workspace bytes the linear layers cut K into fewer
+   ranges).
    Constraints: S, S_ctx >= 1; D = C / heads in {64, 128}; C a multiple of
    512 (at most 2048); F a multiple of 64.  Allocates nothing. */
 regenvc_status regenvc_dit_block_fwd(float *x, const float *e, const regenvc_dit_params *p,

@@ -95,6 +95,7 @@ _SIGNATURES = {
     "regenvc_vae_blend": [ctypes.c_void_p, ctypes.c_void_p, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32,
                           ctypes.c_void_p, ctypes.c_void_p],
     "regenvc_dit_block_workspace": [_i32, _i32, _i32, _i32, _i32, _i32, ctypes.POINTER(ctypes.c_int64)],
+    "regenvc_dit_block_workspace_least": [_i32, _i32, _i32, _i32, _i32, _i32, ctypes.POINTER(ctypes.c_int64)],
     "regenvc_dit_block_fwd": [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                               _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, ctypes.c_void_p,
                               ctypes.c_int64, ctypes.c_void_p],
@@ -139,6 +140,19 @@ def stream_of(device) -> int:
     if raw is not None and device.index is not None:
         return raw(device.index)
     return torch.cuda.current_stream(device).cuda_stream
+
+
+def split_workspace(need: int, device):
+    """`need` bytes for the partial sums of a call that can also run without
+    splitting K, from torch's allocator on the current stream; None where
+    none are needed or the device has no room for them."""
+    import torch
+    if need <= 0:
+        return None
+    try:
+        return torch.empty(need, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
 
 
 _kept = threading.local()

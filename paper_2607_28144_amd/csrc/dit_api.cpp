@@ -111,6 +111,18 @@ regenvc_status check_block_shape(const char *fn, int32_t S, int32_t S_ctx, int32
     return REGENVC_OK;
 }
 
+regenvc_status block_workspace(const char *fn, int32_t S, int32_t S_ctx, int32_t C, int32_t heads, int32_t F,
+                               int32_t n_cu, int64_t BlockLayout::*which, int64_t *bytes)
+{
+    if (bytes == nullptr) return failf(REGENVC_ERR_INVALID_ARG, "%s: bytes is NULL", fn);
+    if (n_cu < 1) return failf(REGENVC_ERR_INVALID_ARG, "%s: n_cu=%d < 1", fn, n_cu);
+    regenvc_status st = check_block_shape(fn, S, S_ctx, C, heads, F);
+    if (st != REGENVC_OK) return st;
+    *bytes = block_layout(S, S_ctx, C, heads, F, n_cu).*which;
+    regenvc::abi::clear_error();
+    return REGENVC_OK;
+}
+
 regenvc_status run_linear(const char *fn, const void *a, int64_t lda, const void *w, const void *bias,
                           const float *gate, void *out, int64_t ldo, int32_t M, int32_t N, int32_t K, int32_t epilogue,
                           void *ws, int64_t ws_bytes, void *stream)
@@ -249,14 +261,14 @@ regenvc_status regenvc_dit_modulation(const void *w_mod, const void *b_mod, cons
 regenvc_status regenvc_dit_block_workspace(int32_t S, int32_t S_ctx, int32_t C, int32_t heads, int32_t F,
                                            int32_t n_cu, int64_t *bytes)
 {
-    const char *fn = "regenvc_dit_block_workspace";
-    if (bytes == nullptr) return failf(REGENVC_ERR_INVALID_ARG, "%s: bytes is NULL", fn);
-    if (n_cu < 1) return failf(REGENVC_ERR_INVALID_ARG, "%s: n_cu=%d < 1", fn, n_cu);
-    regenvc_status st = check_block_shape(fn, S, S_ctx, C, heads, F);
-    if (st != REGENVC_OK) return st;
-    *bytes = block_layout(S, S_ctx, C, heads, F, n_cu).total;
-    regenvc::abi::clear_error();
-    return REGENVC_OK;
+    return block_workspace("regenvc_dit_block_workspace", S, S_ctx, C, heads, F, n_cu, &BlockLayout::total, bytes);
+}
+
+regenvc_status regenvc_dit_block_workspace_least(int32_t S, int32_t S_ctx, int32_t C, int32_t heads, int32_t F,
+                                                 int32_t n_cu, int64_t *bytes)
+{
+    return block_workspace("regenvc_dit_block_workspace_least", S, S_ctx, C, heads, F, n_cu, &BlockLayout::least,
+                           bytes);
 }
 
 regenvc_status regenvc_dit_block_fwd(float *x, const float *e, const regenvc_dit_params *p, const void *ctx_k,

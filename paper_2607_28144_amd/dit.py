@@ -62,7 +62,8 @@ def linear_fwd(a: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor] = 
     """y = a w^T (+ bias) with a fused epilogue (regenvc_linear_fwd_ws):
     'bias' -> bf16 out, 'bias_gelu' -> bf16 gelu_tanh(y), 'gated_residual' ->
     out (float32, required) += gate * y.  The workspace of the split-K form is
-    a torch allocation on the current stream."""
+    a torch allocation on the current stream; without room for it K is not
+    split."""
     M, K = a.shape
     N = w.shape[0]
     lda = _rows(a, "a", torch.bfloat16)
@@ -75,10 +76,11 @@ def linear_fwd(a: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor] = 
         out = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
     ldo = _rows(out, "out", torch.float32 if epi == 2 else torch.bfloat16)
     need = linear_workspace_bytes(M, N, K, epilogue, a.device)
-    ws = torch.empty(need, dtype=torch.uint8, device=a.device) if need > 0 else None
+    ws = _lib.split_workspace(need, a.device)
     st = _lib.load().regenvc_linear_fwd_ws(a.data_ptr(), lda, w.data_ptr(), _vec(bias, "bias", torch.bfloat16, N),
                                            _vec(gate, "gate", torch.float32, N), out.data_ptr(), ldo, M, N, K, epi,
-                                           ws.data_ptr() if ws is not None else None, need, _stream(a.device))
+                                           ws.data_ptr() if ws is not None else None, need if ws is not None else 0,
+                                           _stream(a.device))
     _lib.check(st, "regenvc_linear_fwd_ws")
     return out
 
@@ -149,11 +151,13 @@ class DitBlock:
         self._ws = {}    # (device index, S, S_ctx) -> a workspace for such calls in place of their own
         self._need = {}  # (device index, S, S_ctx) -> workspace bytes
 
-    def workspace_bytes(self, S: int, S_ctx: int, device) -> int:
+    def workspace_bytes(self, S: int, S_ctx: int, device, least: bool = False) -> int:
+        """Workspace bytes of a forward pass (regenvc_dit_block_workspace), or
+        the fewest that it takes (regenvc_dit_block_workspace_least)."""
         n_cu = torch.cuda.get_device_properties(device).multi_processor_count
         out = ctypes.c_int64()
-        st = _lib.load().regenvc_dit_block_workspace(S, S_ctx, self.C, self.heads, self.F, n_cu, ctypes.byref(out))
-        _lib.check(st, "regenvc_dit_block_workspace")
+        fn = "regenvc_dit_block_workspace_least" if least else "regenvc_dit_block_workspace"
+        _lib.check(getattr(_lib.load(), fn)(S, S_ctx, self.C, self.heads, self.F, n_cu, ctypes.byref(out)), fn)
         return out.value
 
     def _workspace(self, S: int, S_ctx: int, device) -> torch.Tensor:
@@ -167,7 +171,10 @@ class DitBlock:
             if len(self._need) >= 4096:
                 self._need.clear()
             self._need[key] = need
-        return torch.empty(need, dtype=torch.uint8, device=device)
+        try:
+            return torch.empty(need, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:  # without the linear layers' partial sums
+            return torch.empty(self.workspace_bytes(S, S_ctx, device, least=True), dtype=torch.uint8, device=device)
 
     def forward(self, x: torch.Tensor, e: torch.Tensor, ctx_k: torch.Tensor, ctx_v: torch.Tensor, grid,
                 token0: int = 0) -> torch.Tensor:

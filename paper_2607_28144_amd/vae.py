@@ -57,7 +57,7 @@ def conv3d(x: torch.Tensor, w: torch.Tensor, b: torch.Tensor, tiles, Hr: int, Wr
     or the tiles' buffers [n, T, Hr, Wr, Cin] (plane_hw = (H, W), the plane's
     size).  Returns [n, T, Hr, Wr, Cout].  split_k: hand the library the
     workspace of its split-K form (a torch allocation), used when the tiles
-    alone would leave the GPU mostly idle."""
+    alone would leave the GPU mostly idle and there is room for it."""
     for name, t in (("x", x), ("w", w), ("b", b)):
         _check(t, name)
     n = len(tiles)
@@ -76,10 +76,11 @@ def conv3d(x: torch.Tensor, w: torch.Tensor, b: torch.Tensor, tiles, Hr: int, Wr
     out = torch.empty((n, T, Hr, Wr, Cout), dtype=torch.bfloat16, device=x.device)
     arr = (_lib.VaeTile * n)(*tiles)
     need = conv3d_workspace_bytes(T, Hr, Wr, n, Cin, Cout, x.device) if split_k else 0
-    ws = torch.empty(need, dtype=torch.uint8, device=x.device) if need > 0 else None
+    ws = _lib.split_workspace(need, x.device)
     st = _lib.load().regenvc_vae_conv3d_fwd(x.data_ptr(), is_plane, w.data_ptr(), b.data_ptr(), int(silu),
                                             out.data_ptr(), T, H, W, Cin, Cout, arr, n, Hr, Wr,
-                                            ws.data_ptr() if ws is not None else None, need, _stream(x.device))
+                                            ws.data_ptr() if ws is not None else None, need if ws is not None else 0,
+                                            _stream(x.device))
     _lib.check(st, "regenvc_vae_conv3d_fwd")
     return out
 

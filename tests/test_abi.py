@@ -382,3 +382,20 @@ def test_linear_workspace(lib):
     assert call(FAKE + (3 << 20) + 128, 4096) == _lib.ERR_UNSUPPORTED
     for base in (FAKE, FAKE + (1 << 20), FAKE + (2 << 20)):
         assert call(base, 4096) == _lib.ERR_INVALID_ARG
+
+
+def test_block_workspace_least(lib):
+    """The least workspace of a block call leaves out the linear layers' partial
+    sums, and both queries refuse the same sizes."""
+    def need(fn, *args):
+        b = ctypes.c_int64(-1)
+        return getattr(lib, fn)(*args, 256, ctypes.byref(b)), b.value
+    for S in (64, 336, 1560, 10920):
+        (st, total), (st2, least) = (need("regenvc_dit_block_workspace" + s, S, 512, 1536, 12, 8960) for s in ("", "_least"))
+        assert st == st2 == _lib.OK
+        activations = 6 * 1536 * 4 + S * (5 * 1536 + 8960) * 2
+        assert activations <= least <= total
+        assert (least < total) == (S < 10920)  # the window's layers do not split
+    for args in [(0, 512, 1536, 12, 8960), (64, 512, 1500, 12, 8960), (64, 512, 1536, 10, 8960), (64, 512, 1536, 12, 100)]:
+        a, b = need("regenvc_dit_block_workspace", *args), need("regenvc_dit_block_workspace_least", *args)
+        assert a == b and a[0] != _lib.OK

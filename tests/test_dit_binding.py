@@ -78,3 +78,51 @@ def test_no_workspace_is_held_between_calls(block):
         call(s)
     assert [n for _, n in lib.calls] == [256 * s for s in range(1, 30)]
     assert blk._ws == {} and all(isinstance(v, int) for v in blk._need.values())
+
+
+class NoRoom:
+    """torch.empty for a device whose memory holds no byte buffer above `limit`."""
+
+    def __init__(self, limit):
+        self.limit, self.empty = limit, torch.empty
+
+    def __call__(self, *size, dtype=None, device=None, **kw):
+        if dtype == torch.uint8 and size[0] > self.limit:
+            raise torch.OutOfMemoryError("no room")
+        return self.empty(*size, dtype=dtype, **kw)
+
+
+def test_block_without_room_for_partial_sums_runs_in_the_least_workspace(block, monkeypatch):
+    _, use, call = block
+    lib = use(Recorder())
+    lib.regenvc_dit_block_workspace_least = lambda *a: setattr(a[-1]._obj, "value", 256) or _lib.OK
+    monkeypatch.setattr(torch, "empty", NoRoom(1000))
+    call()
+    assert [n for _, n in lib.calls] == [256]
+
+
+def test_linear_and_convolution_without_room_for_partial_sums_do_not_split(monkeypatch):
+    """A call that can run without its workspace is not refused for want of it."""
+    from paper_2607_28144_amd import dit, vae
+    given = []
+
+    class Lib:
+        def regenvc_linear_fwd_ws(self, *args):
+            given.append(args[-3:-1])
+            return _lib.OK
+
+        def regenvc_vae_conv3d_fwd(self, *args):
+            given.append(args[-3:-1])
+            return _lib.OK
+    monkeypatch.setattr(_lib, "load", lambda: Lib())
+    monkeypatch.setattr(torch, "empty", NoRoom(1000))
+    for m in (dit, vae):
+        monkeypatch.setattr(m, "_stream", lambda device: None)
+    monkeypatch.setattr(dit, "_rows", lambda t, *a: t.stride(0))
+    monkeypatch.setattr(dit, "linear_workspace_bytes", lambda *a: 4096)
+    monkeypatch.setattr(vae, "_check", lambda *a: None)
+    monkeypatch.setattr(vae, "conv3d_workspace_bytes", lambda *a: 4096)
+    dit.linear_fwd(torch.zeros(4, 64, dtype=torch.bfloat16), torch.zeros(16, 64, dtype=torch.bfloat16))
+    vae.conv3d(torch.zeros(1, 2, 3, 64, dtype=torch.bfloat16), torch.zeros(64, 3, 3, 3, 64, dtype=torch.bfloat16),
+               torch.zeros(64, dtype=torch.bfloat16), [_lib.VaeTile(0, 2, 0, 3, 0, 2, 0, 3)], 2, 3)
+    assert given == [(None, 0), (None, 0)]
