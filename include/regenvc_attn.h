@@ -332,6 +332,14 @@ typedef struct {
 regenvc_status regenvc_attn_plan_query(int32_t B, int32_t H, int32_t Sq, int32_t Skv, int32_t D,
                                        int32_t n_cu, regenvc_attn_plan *plan);
 
+/* The decomposition of a matrix product (regenvc_linear_plan_query,
+   regenvc_vae_conv3d_plan_query): output tiles of rows x cols, one per
+   workgroup of `waves` waves, K in k_ranges contiguous ranges (1: not split;
+   more: f32 partial sums in the workspace and a second kernel). */
+typedef struct {
+    int32_t rows, cols, waves, k_ranges;
+} regenvc_tile_plan;
+
 /* Work plan of one regenvc_cross_attn_dual_fwd call: as
    regenvc_attn_plan_query, with key_tiles the tiles of both contexts and
    key_ranges the ranges of a split tile over both (S_txt, S_img >= 1). */

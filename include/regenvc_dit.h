@@ -80,6 +80,12 @@ regenvc_status regenvc_linear_fwd_ws(const void *a, int64_t lda, const void *w, 
 regenvc_status regenvc_linear_workspace(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t n_cu,
                                         int64_t *bytes);
 
+/* The decomposition of such a call with rows of a less than 2^22 elements
+   apart, with workspace_bytes of workspace (INT64_MAX: as many as it can
+   use).  Host-only. */
+regenvc_status regenvc_linear_plan_query(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t n_cu,
+                                         int64_t workspace_bytes, regenvc_tile_plan *plan);
+
 /* Layer normalization of the f32 rows of x [rows, C] (row stride ldx) into
    bf16 y (row stride ldy): LN(x) (1 + scale) + shift with f32 shift, scale
    [C] (the adaLN-modulated form; w, b NULL), or LN(x) w + b with bf16 w, b

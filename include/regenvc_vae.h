@@ -86,6 +86,12 @@ regenvc_status regenvc_vae_conv3d_fwd(const void *in, int32_t in_is_plane, const
 regenvc_status regenvc_vae_conv3d_workspace(int32_t T, int32_t Hr, int32_t Wr, int32_t n_tiles, int32_t Cin,
                                             int32_t Cout, int32_t n_cu, int64_t *bytes);
 
+/* The decomposition of such a call with workspace_bytes of workspace
+   (INT64_MAX: as many as it can use).  Host-only; sizes as above. */
+regenvc_status regenvc_vae_conv3d_plan_query(int32_t T, int32_t Hr, int32_t Wr, int32_t n_tiles, int32_t Cin,
+                                             int32_t Cout, int32_t n_cu, int64_t workspace_bytes,
+                                             regenvc_tile_plan *plan);
+
 /* Blended gather: out (bf16 [T, H, W, C]) = sum over the tiles covering each
    pixel of ramp_row x ramp_col x tile value, from the tiles' outputs bf16
    [n_tiles][T][Hr][Wr][C].  The tiles must be those of one regenvc_vae_split

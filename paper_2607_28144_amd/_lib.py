@@ -26,6 +26,11 @@ class AttnPlan(ctypes.Structure):
                 ("tile_rows", ctypes.c_int32)]
 
 
+class TilePlan(ctypes.Structure):
+    """regenvc_tile_plan: the decomposition of a matrix product."""
+    _fields_ = [(n, ctypes.c_int32) for n in ("rows", "cols", "waves", "k_ranges")]
+
+
 class VaeTile(ctypes.Structure):
     """regenvc_vae_tile: a tile's core and region (half-open row/column ranges)."""
     _fields_ = [(n, ctypes.c_int32) for n in ("core_y0", "core_y1", "core_x0", "core_x1",
@@ -79,6 +84,7 @@ _SIGNATURES = {
                               ctypes.c_void_p, ctypes.c_int64, _i32, _i32, _i32, _i32, ctypes.c_void_p,
                               ctypes.c_int64, ctypes.c_void_p],
     "regenvc_linear_workspace": [_i32, _i32, _i32, _i32, _i32, ctypes.POINTER(ctypes.c_int64)],
+    "regenvc_linear_plan_query": [_i32, _i32, _i32, _i32, _i32, ctypes.c_int64, ctypes.POINTER(TilePlan)],
     "regenvc_layer_norm_fwd": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p,
                                ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, _i32, _i32, ctypes.c_float,
                                ctypes.c_void_p],
@@ -92,6 +98,8 @@ _SIGNATURES = {
                                _i32, _i32, _i32, _i32, _i32, ctypes.c_void_p, _i32, _i32, _i32, ctypes.c_void_p,
                                ctypes.c_int64, ctypes.c_void_p],
     "regenvc_vae_conv3d_workspace": [_i32, _i32, _i32, _i32, _i32, _i32, _i32, ctypes.POINTER(ctypes.c_int64)],
+    "regenvc_vae_conv3d_plan_query": [_i32, _i32, _i32, _i32, _i32, _i32, _i32, ctypes.c_int64,
+                                      ctypes.POINTER(TilePlan)],
     "regenvc_vae_blend": [ctypes.c_void_p, ctypes.c_void_p, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32,
                           ctypes.c_void_p, ctypes.c_void_p],
     "regenvc_dit_block_workspace": [_i32, _i32, _i32, _i32, _i32, _i32, ctypes.POINTER(ctypes.c_int64)],

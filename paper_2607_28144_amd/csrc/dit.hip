@@ -366,17 +366,18 @@ hipError_t launch_linear4(const LinearArgs &a, int splits, hipStream_t stream)
 // one round where 43 row blocks of 256 need 258 tiles).
 TilePlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes)
 {
+    if (K == 0 || K >= kWideStride) return TilePlan{kTile128x128, 1, 128, 128, 4};
     // fixed times by tile and epilogue
     static const double kFixed[7][3] = {{5.0, 9.0, 9.0},  {8.3, 13.7, 20.0}, {6.2, 9.0, 14.0}, {5.1, 8.6, 13.2},
                                         {3.2, 4.5, 8.5},  {1.0, 2.3, 4.0},   {1.0, 2.0, 2.8}};
     const TileCost costs[] = {
-        {kTile288x256, 288, 256, kFixed[0][epi], 0.0, 1.274, 1.254, false},
-        {kTile256x256, 256, 256, kFixed[1][epi], kFixed[1][0], 0.99, 1.188, true},
-        {kTile160x256, 160, 256, kFixed[2][epi], kFixed[2][0], 0.668, 1.188, true},
-        {kTile192x192, 192, 192, kFixed[3][epi], kFixed[3][0], 0.645, 1.188, true},
-        {kTile128x192, 128, 192, kFixed[4][epi], kFixed[4][0], 0.52, 1.15, true},
-        {kTile128x128, 128, 128, kFixed[5][epi], kFixed[5][0], 0.448, 0.921, true},
-        {kTile64x128, 64, 128, kFixed[6][epi], kFixed[6][0], 0.43, 1.0, true},
+        {kTile288x256, 288, 256, 8, kFixed[0][epi], 0.0, 1.274, 1.254, false},
+        {kTile256x256, 256, 256, 4, kFixed[1][epi], kFixed[1][0], 0.99, 1.188, true},
+        {kTile160x256, 160, 256, 4, kFixed[2][epi], kFixed[2][0], 0.668, 1.188, true},
+        {kTile192x192, 192, 192, 4, kFixed[3][epi], kFixed[3][0], 0.645, 1.188, true},
+        {kTile128x192, 128, 192, 4, kFixed[4][epi], kFixed[4][0], 0.52, 1.15, true},
+        {kTile128x128, 128, 128, 4, kFixed[5][epi], kFixed[5][0], 0.448, 0.921, true},
+        {kTile64x128, 64, 128, 4, kFixed[6][epi], kFixed[6][0], 0.43, 1.0, true},
     };
     return plan_tiles(costs, SplitCost{8.5, 5.0e6, epi == kEpiGatedRes ? 8 : 2}, M, N, K / kBK, n_cu, ws_bytes);
 }
@@ -391,6 +392,7 @@ size_t linear_workspace_bytes(int M, int N, int K, int epi, int n_cu)
 hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
 {
     if (a.M == 0 || a.N == 0) return hipSuccess;
+    // no steps at all, or strides for which the offsets within a tile may leave 32 bits
     if (a.K == 0 || a.lda >= kWideStride || a.K >= kWideStride) return launch_linear4<Tile128x128, true>(a, 1, stream);
     const TilePlan p = linear_plan(a.M, a.N, a.K, a.epi, device_cu_count(), a.ws != nullptr ? a.ws_bytes : 0);
     switch (p.tile) {

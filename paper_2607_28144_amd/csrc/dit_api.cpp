@@ -111,6 +111,17 @@ regenvc_status check_block_shape(const char *fn, int32_t S, int32_t S_ctx, int32
     return REGENVC_OK;
 }
 
+regenvc_status check_linear_query(const char *fn, int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t n_cu)
+{
+    if (M < 0 || N < 0 || K < 0 || n_cu < 1)
+        return failf(REGENVC_ERR_INVALID_ARG, "%s: bad size (M=%d N=%d K=%d n_cu=%d)", fn, M, N, K, n_cu);
+    if (epilogue != REGENVC_EPI_BIAS && epilogue != REGENVC_EPI_BIAS_GELU && epilogue != REGENVC_EPI_GATED_RESIDUAL)
+        return failf(REGENVC_ERR_INVALID_ARG, "%s: unknown epilogue %d", fn, epilogue);
+    if (K % 64 != 0 || N % 16 != 0)
+        return failf(REGENVC_ERR_UNSUPPORTED, "%s: K=%d must be a multiple of 64, N=%d of 16", fn, K, N);
+    return REGENVC_OK;
+}
+
 regenvc_status block_workspace(const char *fn, int32_t S, int32_t S_ctx, int32_t C, int32_t heads, int32_t F,
                                int32_t n_cu, int64_t BlockLayout::*which, int64_t *bytes)
 {
@@ -174,13 +185,23 @@ regenvc_status regenvc_linear_workspace(int32_t M, int32_t N, int32_t K, int32_t
 {
     const char *fn = "regenvc_linear_workspace";
     if (bytes == nullptr) return failf(REGENVC_ERR_INVALID_ARG, "%s: bytes is NULL", fn);
-    if (M < 0 || N < 0 || K < 0 || n_cu < 1)
-        return failf(REGENVC_ERR_INVALID_ARG, "%s: bad size (M=%d N=%d K=%d n_cu=%d)", fn, M, N, K, n_cu);
-    if (epilogue != REGENVC_EPI_BIAS && epilogue != REGENVC_EPI_BIAS_GELU && epilogue != REGENVC_EPI_GATED_RESIDUAL)
-        return failf(REGENVC_ERR_INVALID_ARG, "%s: unknown epilogue %d", fn, epilogue);
-    if (K % 64 != 0 || N % 16 != 0)
-        return failf(REGENVC_ERR_UNSUPPORTED, "%s: K=%d must be a multiple of 64, N=%d of 16", fn, K, N);
+    const regenvc_status st = check_linear_query(fn, M, N, K, epilogue, n_cu);
+    if (st != REGENVC_OK) return st;
     *bytes = (int64_t)regenvc::linear_workspace_bytes(M, N, K, epilogue, n_cu);
+    regenvc::abi::clear_error();
+    return REGENVC_OK;
+}
+
+regenvc_status regenvc_linear_plan_query(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t n_cu,
+                                         int64_t workspace_bytes, regenvc_tile_plan *plan)
+{
+    const char *fn = "regenvc_linear_plan_query";
+    if (plan == nullptr) return failf(REGENVC_ERR_INVALID_ARG, "%s: plan is NULL", fn);
+    if (workspace_bytes < 0) return failf(REGENVC_ERR_INVALID_ARG, "%s: workspace_bytes < 0", fn);
+    const regenvc_status st = check_linear_query(fn, M, N, K, epilogue, n_cu);
+    if (st != REGENVC_OK) return st;
+    const regenvc::TilePlan p = regenvc::linear_plan(M, N, K, epilogue, n_cu, workspace_bytes);
+    *plan = regenvc_tile_plan{p.bm, p.bn, p.waves, p.splits};
     regenvc::abi::clear_error();
     return REGENVC_OK;
 }

@@ -13,7 +13,7 @@ namespace regenvc {
 // round, and the factor by which full rounds are slower (the clock that the
 // power limit leaves, shared LDS and memory).
 struct TileCost {
-    int32_t tile, bm, bn;
+    int32_t tile, bm, bn, waves;
     double fixed, fixed_split, step, load;
     bool splits;  // has a split-K form
 };
@@ -25,6 +25,7 @@ struct SplitCost {
 };
 struct TilePlan {
     int32_t tile, splits;
+    int32_t bm, bn, waves;
 };
 
 // The tile and number of K ranges (at most 8, of at least 8 steps each) with
@@ -36,7 +37,7 @@ TilePlan plan_tiles(const TileCost (&costs)[N_COSTS], const SplitCost &sc, int64
                     int64_t ws_bytes)
 {
     const int64_t plane = M * N * (int64_t)sizeof(float);
-    TilePlan best{costs[0].tile, 1};
+    TilePlan best{costs[0].tile, 1, costs[0].bm, costs[0].bn, costs[0].waves};
     double best_t = INFINITY;
     for (const TileCost &c : costs) {
         const int64_t tiles = (M + c.bm - 1) / c.bm * ((N + c.bn - 1) / c.bn);
@@ -49,7 +50,7 @@ TilePlan plan_tiles(const TileCost (&costs)[N_COSTS], const SplitCost &sc, int64
             double t = (double)full * one * c.load;
             if (rest > 0) t += one * (1.0 + (c.load - 1.0) * (double)rest / n_cu);
             if (s > 1) t += sc.launch + ((double)plane * 2 * s + (double)M * N * (double)sc.out_bytes) / sc.rate;
-            if (t < best_t) best_t = t, best = TilePlan{c.tile, s};
+            if (t < best_t) best_t = t, best = TilePlan{c.tile, s, c.bm, c.bn, c.waves};
         }
     }
     return best;

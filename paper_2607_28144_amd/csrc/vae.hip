@@ -66,6 +66,10 @@ __device__ __forceinline__ int div_by(int n, int d, uint32_t inv, int &rem)
 // taps outermost they came from beyond it.
 constexpr int kTaps = 27;
 
+// Input channels from which the offsets within a tile's weight rows (255 rows
+// of 27 Cin elements) may leave 32 bits.
+constexpr int kWideCin = (1 << 22) / kTaps + 1;
+
 // Weight rows [27, Cin] in that order.
 template <bool WIDE>
 struct ConvW : tile::Dense<WIDE> {
@@ -290,13 +294,19 @@ hipError_t launch_conv(const ConvArgs &a, int splits, hipStream_t stream)
 TilePlan conv_plan(int64_t M, int N, int Cin, int n_cu, int64_t ws_bytes)
 {
     static const TileCost kCosts[] = {
-        {kConv256x256, 256, 256, 15.0, 15.0, 1.20, 1.15, true},
-        {kConv256x192, 256, 192, 12.2, 12.2, 0.947, 1.15, true},
-        {kConv192x192, 192, 192, 10.9, 10.9, 0.75, 1.15, true},
-        {kConv128x192, 128, 192, 7.6, 7.6, 0.569, 1.15, true},
-        {kConv128x128, 128, 128, 2.0, 2.0, 0.45, 1.05, true},
+        {kConv256x256, 256, 256, 4, 15.0, 15.0, 1.20, 1.15, true},
+        {kConv256x192, 256, 192, 4, 12.2, 12.2, 0.947, 1.15, true},
+        {kConv192x192, 192, 192, 4, 10.9, 10.9, 0.75, 1.15, true},
+        {kConv128x192, 128, 192, 4, 7.6, 7.6, 0.569, 1.15, true},
+        {kConv128x128, 128, 128, 4, 2.0, 2.0, 0.45, 1.05, true},
     };
-    return plan_tiles(kCosts, SplitCost{3.0, 7.0e6, 2}, M, N, kTaps * (Cin / kBK), n_cu, ws_bytes);
+    const SplitCost split{3.0, 7.0e6, 2};
+    const int nk = kTaps * (Cin / kBK);
+    if (Cin >= kWideCin) {  // the one tile that such weight rows have
+        const TileCost wide[] = {kCosts[4]};
+        return plan_tiles(wide, split, M, N, nk, n_cu, ws_bytes);
+    }
+    return plan_tiles(kCosts, split, M, N, nk, n_cu, ws_bytes);
 }
 
 size_t conv_workspace_bytes(int64_t M, int N, int Cin, int n_cu)
@@ -317,8 +327,7 @@ hipError_t launch_vae_conv(const ConvArgs &args, hipStream_t stream)
     a.tap0 = -2 * frame - row - px;  // tap (-2, -1, -1)
     a.row_jump = row - 3 * px, a.frame_jump = frame - 3 * row;
     const TilePlan p = conv_plan(M, a.Cout, a.Cin, device_cu_count(), a.ws != nullptr ? a.ws_bytes : 0);
-    // weight rows so long that a tile's offsets may leave 32 bits
-    if ((int64_t)27 * a.Cin >= (1 << 22)) return launch_conv<Tile128x128, true>(a, p.splits, stream);
+    if (a.Cin >= kWideCin) return launch_conv<Tile128x128, true>(a, p.splits, stream);
     switch (p.tile) {
     case kConv256x256: return launch_conv<Tile256x256>(a, p.splits, stream);
     case kConv256x192: return launch_conv<Tile256x192>(a, p.splits, stream);

@@ -39,6 +39,17 @@ regenvc_status check_tiles(const char *fn, const regenvc_vae_tile *t, int32_t n,
     return REGENVC_OK;
 }
 
+regenvc_status check_conv_query(const char *fn, int32_t T, int32_t Hr, int32_t Wr, int32_t n_tiles, int32_t Cin,
+                                int32_t Cout, int32_t n_cu)
+{
+    if (T < 1 || Hr < 1 || Wr < 1 || n_tiles < 1 || n_tiles > REGENVC_VAE_MAX_TILES || n_cu < 1)
+        return failf(REGENVC_ERR_INVALID_ARG, "%s: bad sizes (T=%d Hr=%d Wr=%d n_tiles=%d n_cu=%d)", fn, T, Hr, Wr,
+                     n_tiles, n_cu);
+    if (Cin < 64 || Cout < 64 || Cin % 64 || Cout % 64)
+        return failf(REGENVC_ERR_UNSUPPORTED, "%s: channels Cin=%d Cout=%d must be multiples of 64", fn, Cin, Cout);
+    return REGENVC_OK;
+}
+
 void copy_tiles(regenvc::VaeTile *dst, const regenvc_vae_tile *src, int n)
 {
     for (int i = 0; i < n; ++i)
@@ -125,12 +136,24 @@ regenvc_status regenvc_vae_conv3d_workspace(int32_t T, int32_t Hr, int32_t Wr, i
 {
     const char *fn = "regenvc_vae_conv3d_workspace";
     if (bytes == nullptr) return failf(REGENVC_ERR_INVALID_ARG, "%s: bytes is NULL", fn);
-    if (T < 1 || Hr < 1 || Wr < 1 || n_tiles < 1 || n_tiles > REGENVC_VAE_MAX_TILES || n_cu < 1)
-        return failf(REGENVC_ERR_INVALID_ARG, "%s: bad sizes (T=%d Hr=%d Wr=%d n_tiles=%d n_cu=%d)", fn, T, Hr, Wr,
-                     n_tiles, n_cu);
-    if (Cin < 64 || Cout < 64 || Cin % 64 || Cout % 64)
-        return failf(REGENVC_ERR_UNSUPPORTED, "%s: channels Cin=%d Cout=%d must be multiples of 64", fn, Cin, Cout);
+    const regenvc_status st = check_conv_query(fn, T, Hr, Wr, n_tiles, Cin, Cout, n_cu);
+    if (st != REGENVC_OK) return st;
     *bytes = (int64_t)regenvc::conv_workspace_bytes((int64_t)n_tiles * T * Hr * Wr, Cout, Cin, n_cu);
+    regenvc::abi::clear_error();
+    return REGENVC_OK;
+}
+
+regenvc_status regenvc_vae_conv3d_plan_query(int32_t T, int32_t Hr, int32_t Wr, int32_t n_tiles, int32_t Cin,
+                                             int32_t Cout, int32_t n_cu, int64_t workspace_bytes,
+                                             regenvc_tile_plan *plan)
+{
+    const char *fn = "regenvc_vae_conv3d_plan_query";
+    if (plan == nullptr) return failf(REGENVC_ERR_INVALID_ARG, "%s: plan is NULL", fn);
+    if (workspace_bytes < 0) return failf(REGENVC_ERR_INVALID_ARG, "%s: workspace_bytes < 0", fn);
+    const regenvc_status st = check_conv_query(fn, T, Hr, Wr, n_tiles, Cin, Cout, n_cu);
+    if (st != REGENVC_OK) return st;
+    const regenvc::TilePlan p = regenvc::conv_plan((int64_t)n_tiles * T * Hr * Wr, Cout, Cin, n_cu, workspace_bytes);
+    *plan = regenvc_tile_plan{p.bm, p.bn, p.waves, p.splits};
     regenvc::abi::clear_error();
     return REGENVC_OK;
 }

@@ -1,0 +1,74 @@
+"""Host-only tests of the decomposition of the matrix products
+(regenvc_linear_plan_query, regenvc_vae_conv3d_plan_query): the queries make
+no HIP call, so a device of 256 compute units is assumed."""
+import ctypes
+
+import pytest
+
+from paper_2607_28144_amd import _lib
+
+N_CU = 256
+ALL = 2 ** 63 - 1  # as much workspace as the call can use
+
+
+def linear_plan(M, N, K, epi, ws=ALL, n_cu=N_CU):
+    p = _lib.TilePlan()
+    _lib.check(_lib.load().regenvc_linear_plan_query(M, N, K, epi, n_cu, ws, ctypes.byref(p)), "plan query")
+    return p.rows, p.cols, p.waves, p.k_ranges
+
+
+def conv_plan(T, H, W, Cin, Cout, ws=ALL, n_cu=N_CU):
+    p = _lib.TilePlan()
+    _lib.check(_lib.load().regenvc_vae_conv3d_plan_query(T, H, W, 1, Cin, Cout, n_cu, ws, ctypes.byref(p)), "plan query")
+    return p.rows, p.cols, p.waves, p.k_ranges
+
+
+def linear_bytes(M, N, K, epi):
+    b = ctypes.c_int64()
+    _lib.check(_lib.load().regenvc_linear_workspace(M, N, K, epi, N_CU, ctypes.byref(b)), "workspace query")
+    return b.value
+
+
+def conv_bytes(T, H, W, Cin, Cout):
+    b = ctypes.c_int64()
+    _lib.check(_lib.load().regenvc_vae_conv3d_workspace(T, H, W, 1, Cin, Cout, N_CU, ctypes.byref(b)), "workspace query")
+    return b.value
+
+
+@pytest.mark.parametrize("epi", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(1, 16, 64), (300, 1536, 8960), (1365, 1536, 8960), (700, 1552, 8896), (10920, 4608, 1536),
+                                   (65520, 5120, 5120), (300, 16, 1 << 22), (300, 16, 0)])
+def test_linear_ranges_and_workspace_agree(M, N, K, epi):
+    """One f32 plane of the output per range, at least 8 K steps in each, at
+    most 8 ranges, fewer where the workspace holds fewer planes."""
+    ranges = linear_plan(M, N, K, epi)[3]
+    assert 1 <= ranges <= 8 and (ranges == 1 or K // 64 >= 8 * ranges)
+    assert linear_bytes(M, N, K, epi) == (ranges * M * N * 4 if ranges > 1 else 0)
+    for planes in range(9):
+        assert linear_plan(M, N, K, epi, planes * M * N * 4 + 255)[3] <= max(1, planes)
+
+
+@pytest.mark.parametrize("T,H,W,Cin,Cout", [(1, 17, 19, 64, 64), (7, 34, 34, 384, 384), (7, 60, 104, 384, 384),
+                                            (1, 2, 3, 155392, 64)])
+def test_conv_ranges_and_workspace_agree(T, H, W, Cin, Cout):
+    rows, cols, _, ranges = conv_plan(T, H, W, Cin, Cout)
+    assert 1 <= ranges <= 8 and (ranges == 1 or 27 * Cin // 64 >= 8 * ranges)
+    assert conv_bytes(T, H, W, Cin, Cout) == (ranges * T * H * W * Cout * 4 if ranges > 1 else 0)
+    for planes in range(9):
+        assert conv_plan(T, H, W, Cin, Cout, planes * T * H * W * Cout * 4 + 255)[3] <= max(1, planes)
+    if 27 * Cin >= 1 << 22:
+        assert (rows, cols) == (128, 128)
+
+
+def test_bad_queries_are_refused():
+    lib, p = _lib.load(), _lib.TilePlan()
+    linear = lambda *a: lib.regenvc_linear_plan_query(*a, ctypes.byref(p))  # noqa: E731
+    conv = lambda *a: lib.regenvc_vae_conv3d_plan_query(*a, ctypes.byref(p))  # noqa: E731
+    for a in [(-1, 16, 64, 0, 256, 0), (1, 16, 64, 3, 256, 0), (1, 16, 64, 0, 0, 0), (1, 16, 64, 0, 256, -1)]:
+        assert linear(*a) == _lib.ERR_INVALID_ARG
+    assert linear(1, 17, 64, 0, 256, 0) == linear(1, 16, 65, 0, 256, 0) == _lib.ERR_UNSUPPORTED
+    assert lib.regenvc_linear_plan_query(1, 16, 64, 0, 256, 0, None) == _lib.ERR_INVALID_ARG
+    for a in [(0, 1, 1, 1, 64, 64, 256, 0), (1, 1, 1, 17, 64, 64, 256, 0), (1, 1, 1, 1, 64, 64, 0, 0), (1, 1, 1, 1, 64, 64, 256, -1)]:
+        assert conv(*a) == _lib.ERR_INVALID_ARG
+    assert conv(1, 1, 1, 1, 65, 64, 256, 0) == _lib.ERR_UNSUPPORTED
+    assert lib.regenvc_vae_conv3d_plan_query(1, 1, 1, 1, 64, 64, 256, 0, None) == _lib.ERR_INVALID_ARG
