@@ -7,7 +7,8 @@
 // Linear layer y = a W^T, a [M, K] and W [N, K] both K-contiguous (the weight
 // layout of a linear layer): the bf16 MFMA tile kernels of gemm_tile.hpp with
 // dense rows, four waves per tile of 64 x 128 to 256 x 256 or eight per
-// 288 x 256, K split over workgroups where the tiles are few (linear_plan).
+// 256 x 256 and 288 x 256, K split over workgroups where the tiles are few
+// (linear_plan).
 #include "dit_kernels.hpp"
 
 #include "attn_kernels.hpp"
@@ -355,31 +356,38 @@ hipError_t launch_linear4(const LinearArgs &a, int splits, hipStream_t stream)
 }  // namespace
 
 // The tile and K split of a linear layer, by plan_tiles; the constants are
-// fitted to 11 row counts from 300 to 10920 of the block's five layers (the
-// choice is on average 1.0 % slower than the best of all tiles and splits).
-// Measured, against 256 x 256 or 288 x 256 by eight waves:
-// 1365 x 1536 x 8960 203 -> 48 us (192 x 192 in four ranges),
-// 1560 x 4608 x 1536 39.7 -> 24.1 us (128 x 128), 4096 x 1536 x 8960 205 -> 99 us
-// (128 x 192), 10920 x 8960 x 1536 with GELU 286 -> 267 us (256 x 256 by four
+// fitted to 1002 launches (18 pairs of N and K from 256 to 14336, 19 row counts
+// from 128 to 65520, three epilogues), each timed on every tile and split: the
+// choice is on average 1.0 % slower than the best of them.  Measured, against
+// 256 x 256 or 288 x 256 by eight waves alone:
+// 1365 x 1536 x 8960 203 -> 47 us (192 x 192 in four ranges),
+// 1560 x 4608 x 1536 39.7 -> 23.5 us (128 x 128), 4096 x 1536 x 8960 205 -> 99 us
+// (128 x 192), 10920 x 8960 x 1536 with GELU 286 -> 254 us (256 x 256 by four
 // waves); 10920 x 4608 and 10920 x 1536 stay with 288 x 256 by eight waves
-// (131 and 45.0 us; the best other tile 136 and 48.4: 228 tiles of 288 rows are
-// one round where 43 row blocks of 256 need 258 tiles).
+// (125 and 43.7 us: 228 tiles of 288 rows are one round where 43 row blocks of
+// 256 need 258 tiles), 32760 x 1536 x 1536 with the residual goes on 256 x 256
+// by four waves (187 us; 288 x 256 218, 256 x 256 by eight 204).  Eight waves
+// stay on 256 x 256 where K is short and the rounds are many, the epilogue much
+// of a tile's time: two waves per SIMD overlap one tile's epilogue with
+// another's steps (65520 x 2048 x 128 75.7 us, the best other tile 80.4;
+// 32760 x 512 x 512 with the residual 34.1 against 36.0).
 TilePlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes)
 {
     if (K == 0 || K >= kWideStride) return TilePlan{kTile128x128, 1, 128, 128, 4};
     // fixed times by tile and epilogue
-    static const double kFixed[7][3] = {{5.0, 9.0, 9.0},  {8.3, 13.7, 20.0}, {6.2, 9.0, 14.0}, {5.1, 8.6, 13.2},
-                                        {3.2, 4.5, 8.5},  {1.0, 2.3, 4.0},   {1.0, 2.0, 2.8}};
+    static const double kFixed[8][3] = {{5.8, 9.5, 19.3}, {4.1, 15.2, 15.6}, {7.7, 10.9, 21.6}, {4.8, 7.2, 15.5},
+                                        {4.4, 6.5, 15.2}, {3.0, 6.8, 12.5},  {1.5, 2.3, 5.2},   {0.9, 1.1, 1.8}};
     const TileCost costs[] = {
-        {kTile288x256, 288, 256, 8, kFixed[0][epi], 0.0, 1.274, 1.254, false},
-        {kTile256x256, 256, 256, 4, kFixed[1][epi], kFixed[1][0], 0.99, 1.188, true},
-        {kTile160x256, 160, 256, 4, kFixed[2][epi], kFixed[2][0], 0.668, 1.188, true},
-        {kTile192x192, 192, 192, 4, kFixed[3][epi], kFixed[3][0], 0.645, 1.188, true},
-        {kTile128x192, 128, 192, 4, kFixed[4][epi], kFixed[4][0], 0.52, 1.15, true},
-        {kTile128x128, 128, 128, 4, kFixed[5][epi], kFixed[5][0], 0.448, 0.921, true},
-        {kTile64x128, 64, 128, 4, kFixed[6][epi], kFixed[6][0], 0.43, 1.0, true},
+        {kTile288x256, 288, 256, 8, kFixed[0][epi], 0.0, 1.222, 1.300, false},
+        {kTile256x256By8, 256, 256, 8, kFixed[1][epi], 0.0, 1.113, 1.380, false},
+        {kTile256x256, 256, 256, 4, kFixed[2][epi], kFixed[2][0], 0.934, 1.325, true},
+        {kTile160x256, 160, 256, 4, kFixed[3][epi], kFixed[3][0], 0.737, 1.198, true},
+        {kTile192x192, 192, 192, 4, kFixed[4][epi], kFixed[4][0], 0.648, 1.217, true},
+        {kTile128x192, 128, 192, 4, kFixed[5][epi], kFixed[5][0], 0.497, 1.199, true},
+        {kTile128x128, 128, 128, 4, kFixed[6][epi], kFixed[6][0], 0.424, 0.988, true},
+        {kTile64x128, 64, 128, 4, kFixed[7][epi], kFixed[7][0], 0.396, 0.951, true},
     };
-    return plan_tiles(costs, SplitCost{8.5, 5.0e6, epi == kEpiGatedRes ? 8 : 2}, M, N, K / kBK, n_cu, ws_bytes);
+    return plan_tiles(costs, SplitCost{5.1, 8.1e6, epi == kEpiGatedRes ? 8 : 2}, M, N, K / kBK, n_cu, ws_bytes);
 }
 
 size_t linear_workspace_bytes(int M, int N, int K, int epi, int n_cu)
@@ -403,6 +411,7 @@ hipError_t launch_linear(const LinearArgs &a, hipStream_t stream)
     case kTile128x192: return launch_linear4<Tile128x192>(a, p.splits, stream);
     case kTile64x128: return launch_linear4<Tile64x128>(a, p.splits, stream);
     case kTile288x256: return launch_linear_bm<288>(a, stream);
+    case kTile256x256By8: return launch_linear_bm<256>(a, stream);
     }
     return hipErrorInvalidValue;
 }

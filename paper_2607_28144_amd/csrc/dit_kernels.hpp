@@ -43,6 +43,7 @@ enum LinearTile : int32_t {
     kTile64x128 = 4,
     kTile288x256 = 5,
     kTile128x192 = 6,
+    kTile256x256By8 = 7,  // by eight waves
 };
 // The plan of this shape on n_cu compute units with ws_bytes of workspace.
 TilePlan linear_plan(int M, int N, int K, int epi, int n_cu, int64_t ws_bytes);

@@ -1,7 +1,8 @@
 // The bf16 MFMA tile kernels of the linear layers of the diffusion block
 // (dense rows) and of the VAE's causal 3D convolution (rows gathered as an
 // implicit GEMM): out[m][n] = epilogue(sum_k A[m][k] W[n][k]).  Four waves per
-// tile (mma4, store4) for most shapes; eight (tile_body) for tiles of 288 rows.
+// tile (mma4, store4) for most shapes; eight (tile_body) for tiles of 288 rows
+// and for some of 256.
 //
 // Eight waves.  Workgroup = 8 waves (two per SIMD) = one BM x BN output tile, BN = 16 NB
 // WN; the waves form an (8 / WN) x WN grid, each owning (BM / (8 / WN)) rows

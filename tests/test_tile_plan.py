@@ -72,3 +72,19 @@ def test_bad_queries_are_refused():
         assert conv(*a) == _lib.ERR_INVALID_ARG
     assert conv(1, 1, 1, 1, 65, 64, 256, 0) == _lib.ERR_UNSUPPORTED
     assert lib.regenvc_vae_conv3d_plan_query(1, 1, 1, 1, 64, 64, 256, 0, None) == _lib.ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("M,N,K,epi,slow", [
+    (32760, 1536, 1536, 2, [(288, 256, 8)]),                  # 218 us; 187 on 256 x 256 by four waves
+    (2730, 8960, 1536, 2, [(288, 256, 8)]),                   # 111; 98
+    (16384, 4608, 1536, 2, [(288, 256, 8)]),                  # 340; 270 to 325 on the others
+    (65520, 2048, 128, 0, [(64, 128, 4), (128, 128, 4)]),     # 88; 76 on 256 x 256 by eight waves
+])
+def test_tiles_measured_slow_are_not_chosen(M, N, K, epi, slow):
+    """Launches for which tiles are known that take 7 to 15 % less time than these."""
+    rows, cols, waves, ranges = linear_plan(M, N, K, epi)
+    assert (rows, cols, waves) not in slow and ranges == 1
+
+
+def test_eight_waves_on_256_rows_where_k_is_short():
+    assert linear_plan(65520, 2048, 128, 0) == linear_plan(32760, 512, 512, 2) == (256, 256, 8, 1)
