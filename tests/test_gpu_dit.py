@@ -99,21 +99,72 @@ def test_linear_epilogues(M, N, K):
                 np.abs(gate) * slack + 2.0 ** -22 * (np.abs(x0) + np.abs(gate * y)) + 1e-7)
 
 
-# one shape or more per tile of the plan, with ragged last rows and channels,
-# the shortest K each can have, and K splits with uneven ranges
-@pytest.mark.parametrize("M,N,K", [(1, 16, 64), (65, 1552, 128), (513, 1536, 192),             # 64 x 128
-                                   (5461, 272, 64), (300, 4624, 1536), (1365, 1536, 1536),     # 128 x 128
-                                   (1001, 8960, 1536), (5460, 1552, 1536),                     # 160 x 256
-                                   (1365, 8976, 1536),                                         # 256 x 256
-                                   (5460, 1536, 1536),                                         # 192 x 192
-                                   (2731, 1552, 1536), (2001, 1536, 8960),                     # 128 x 192, whole and split
-                                   (1365, 1552, 8960), (64, 1536, 8960), (700, 1536, 8896)])   # K split
+# ragged last rows and channels, the shortest K, and K splits with uneven ranges
+@pytest.mark.parametrize("M,N,K", [(1, 16, 64), (65, 1552, 128), (513, 1536, 192),
+                                   (5461, 272, 64), (300, 4624, 1536), (1365, 1536, 1536),
+                                   (1001, 8960, 1536), (5460, 1552, 1536),
+                                   (1365, 8976, 1536),
+                                   (5460, 1536, 1536),
+                                   (2731, 1552, 1536), (2001, 1536, 8960),
+                                   (1365, 1552, 8960), (64, 1536, 8960), (700, 1536, 8896)])
 def test_linear_tiles(M, N, K):
     test_linear_epilogues(M, N, K)
 
 
+# (M, N, K, epilogue) and its plan on 256 compute units (rows, channels and
+# waves of a tile, K ranges): every tile with every epilogue that it is chosen
+# for, and split over K; last rows and channels ragged.  test_tile_plan.py holds the plan to these
+# and the list to every kernel.
+LINEAR_PLANS = [
+    (1, 16, 64, 0, (64, 128, 4, 1)), (65, 1552, 128, 1, (64, 128, 4, 1)), (513, 1536, 192, 2, (64, 128, 4, 1)),
+    (64, 1536, 8960, 0, (64, 128, 4, 8)), (1, 16, 1536, 2, (64, 128, 4, 3)),
+    (5461, 272, 64, 0, (128, 128, 4, 1)), (5461, 272, 64, 1, (128, 128, 4, 1)), (1365, 1536, 1536, 2, (128, 128, 4, 1)),
+    (700, 1536, 8896, 1, (128, 128, 4, 3)), (2731, 16, 4096, 0, (128, 128, 4, 8)),
+    (2731, 1552, 1536, 0, (128, 192, 4, 1)), (10921, 272, 1024, 1, (128, 192, 4, 1)), (10921, 272, 1024, 2, (128, 192, 4, 1)),
+    (1001, 1536, 8960, 0, (128, 192, 4, 4)), (2001, 1536, 8960, 0, (128, 192, 4, 2)), (65, 8976, 8896, 2, (128, 192, 4, 5)),
+    (1001, 8960, 1536, 0, (160, 256, 4, 1)), (5461, 1552, 320, 1, (160, 256, 4, 1)), (5461, 1552, 1024, 2, (160, 256, 4, 1)),
+    (129, 8976, 8896, 0, (160, 256, 4, 7)), (1365, 1552, 8960, 1, (160, 256, 4, 4)),
+    (5461, 1040, 1536, 0, (192, 192, 4, 1)), (5460, 1536, 1536, 1, (192, 192, 4, 1)), (10921, 528, 8896, 2, (192, 192, 4, 1)),
+    (1365, 1536, 8960, 2, (192, 192, 4, 4)), (257, 4624, 8896, 0, (192, 192, 4, 5)),
+    (10921, 1040, 1024, 0, (256, 256, 4, 1)), (1365, 8960, 1536, 1, (256, 256, 4, 1)), (10920, 1024, 8960, 2, (256, 256, 4, 1)),
+    (4097, 1040, 8896, 1, (256, 256, 4, 3)),
+    (10921, 1040, 64, 0, (256, 256, 8, 1)), (10921, 1040, 512, 2, (256, 256, 8, 1)), (1365, 8976, 1536, 2, (256, 256, 8, 1)),
+    (10921, 1536, 64, 0, (288, 256, 8, 1)), (10921, 1536, 128, 1, (288, 256, 8, 1)), (10921, 1536, 320, 2, (288, 256, 8, 1)),
+]
+
+
+@pytest.mark.parametrize("M,N,K,epi,plan", LINEAR_PLANS)
+def test_linear_on_every_tile(M, N, K, epi, plan):
+    """Against float64 on the GPU, within the bounds of the module."""
+    from test_tile_plan import linear_plan
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert n_cu != 256 or linear_plan(M, N, K, epi) == plan
+    r = torch.Generator(device="cuda").manual_seed(M + N + K)
+    rand = lambda *n: torch.randn(*n, generator=r, device="cuda")  # noqa: E731
+    a, w, b, gate = rand(M, K).bfloat16(), (rand(N, K) * 0.02).bfloat16(), (rand(N) * 0.02).bfloat16(), rand(N)
+    x0 = rand(M, N) if epi == 2 else None
+    y = torch.mm(a.double(), w.double().t().contiguous()) + b.double()
+    slack = 2 * ACC * torch.mm(a.double().abs(), w.double().abs().t().contiguous())
+    if epi == 2:
+        got = kern().linear_fwd(a, w, b, "gated_residual", gate=gate, out=x0.clone())
+        g = gate.double()
+        ref, tol = x0.double() + g * y, g.abs() * slack + 2.0 ** -22 * (x0.double().abs() + (g * y).abs()) + 1e-7
+    elif epi == 1:
+        got = kern().linear_fwd(a, w, b, "bias_gelu")
+        ref = 0.5 * y * (1 + torch.tanh((2 / torch.pi) ** 0.5 * (y + 0.044715 * y ** 3)))
+        tol = ULP * ref.abs() + 1.13 * slack + 1e-6
+    else:
+        got = kern().linear_fwd(a, w, b)
+        ref, tol = y, ULP * y.abs() + slack
+    worst = float(((got.double() - ref).abs() / tol).max())
+    print(f"[dit] linear {M}x{N}x{K} epilogue {epi} on {plan}: max err/bound {worst:.3f}", flush=True)
+    assert worst <= 1.0
+
+
 def test_linear_wide_row_stride():
-    """Rows so far apart that a tile's offsets leave 32 bits."""
+    """Rows so far apart that a tile's offsets leave 32 bits: 64-bit addresses
+    on 128 x 128 tiles, the contiguous call on 64 x 128.  Both add the steps of
+    K one after another, in the same order."""
     M, N, K, ld = 300, 272, 192, 1 << 23
     rng = np.random.default_rng(5)
     a, w = bits(rng, (M, K)), bits(rng, (N, K), 0.02)
@@ -122,7 +173,7 @@ def test_linear_wide_row_stride():
     da.copy_(dev_bits(a))
     dw = dev_bits(w)
     got = kern().linear_fwd(da, dw)
-    assert torch.equal(got, kern().linear_fwd(da.contiguous(), dw))  # one tile shape, one K order
+    assert torch.equal(got, kern().linear_fwd(da.contiguous(), dw))
 
 
 def test_linear_split_workspace_sizes():

@@ -88,3 +88,30 @@ def test_tiles_measured_slow_are_not_chosen(M, N, K, epi, slow):
 
 def test_eight_waves_on_256_rows_where_k_is_short():
     assert linear_plan(65520, 2048, 128, 0) == linear_plan(32760, 512, 512, 2) == (256, 256, 8, 1)
+
+
+TILES = [(64, 128, 4), (128, 128, 4), (128, 192, 4), (160, 256, 4), (192, 192, 4), (256, 256, 4), (256, 256, 8), (288, 256, 8)]
+CONV_TILES = [(128, 128, 4), (128, 192, 4), (192, 192, 4), (256, 192, 4), (256, 256, 4)]
+
+
+def test_the_gpu_tests_run_every_linear_kernel():
+    """The shapes of test_linear_on_every_tile are planned as they say, and
+    between them reach every kernel: each tile with each epilogue (eight
+    waves on 256 rows are never chosen for the GELU), each four-wave tile
+    split over K, and the second kernel of a split with each epilogue."""
+    from test_gpu_dit import LINEAR_PLANS
+    assert [linear_plan(*c[:4]) for c in LINEAR_PLANS] == [c[4] for c in LINEAR_PLANS]
+    whole = {(p[:3], epi) for _, _, _, epi, p in LINEAR_PLANS if p[3] == 1}
+    assert whole == {(t, e) for t in TILES for e in range(3)} - {((256, 256, 8), 1)}
+    assert {p[:3] for *_, p in LINEAR_PLANS if p[3] > 1} == {t for t in TILES if t[2] == 4}
+    assert {epi for _, _, _, epi, p in LINEAR_PLANS if p[3] > 1} == {0, 1, 2}
+
+
+def test_the_gpu_tests_run_every_convolution_kernel():
+    """The same for test_conv_tiles, which runs each shape with and without
+    the activation."""
+    from test_gpu_vae import CONV_PLANS
+    assert [conv_plan(*c[:5]) for c in CONV_PLANS] == [c[5] for c in CONV_PLANS]
+    for split in (False, True):
+        assert {p[:3] for *_, p in CONV_PLANS if (p[3] > 1) == split} == set(CONV_TILES)
+    assert any(27 * c[3] >= 1 << 22 for c in CONV_PLANS)
