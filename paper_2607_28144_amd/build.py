@@ -22,11 +22,72 @@ ARCH = "gfx950"
 # read-only operands may then live in AGPRs.  Not for the tile kernels of the
 # linear layers, whose accumulators fill the AGPRs.
 VGPR_FORM = {"attn_fwd.hip"}
+# Sources with tiles whose MFMAs are instructions of their own (inline
+# assembly, around which the compiler places no wait states): their assembly is
+# checked (check_tile_kernels).
+CHECKED = {"dit.hip", "vae.hip"}
 
 
 def hipcc() -> str:
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     return os.path.join(rocm, "bin", "hipcc")
+
+
+def check_tile_kernels(name: str, asm: str) -> int:
+    """Refuses device assembly in which a tile kernel with one wave per SIMD
+    spills, or in which an instruction other than an MFMA touches an
+    accumulator (AGPR) less than 20 wait states after an MFMA or 4 before one,
+    on any path: the compiler places none around its inline MFMAs.  Returns
+    the number of kernels checked; none is an error."""
+    def fail(kernel, what):
+        raise RuntimeError(f"{name}: {what}: {kernel}")
+
+    one_wave = re.compile(r"Shape4I(?:Li\d+E){3}Li1EE")
+    meta = {}
+    for entry in re.split(r"(?m)^  - (?=\.\w+:)", asm)[1:]:
+        keys = dict(re.findall(r"(?m)^\s*(\.\w+):\s+(\S+)\s*$", entry))
+        if ".vgpr_spill_count" in keys:
+            meta[keys[".name"]] = keys
+    count = 0
+    for text in re.split(r"(?m)^(?=_Z\w+:)", asm)[1:]:
+        kernel = text.split(":", 1)[0]
+        code = [ln.split(";")[0].strip() for ln in text.split(".Lfunc_end", 1)[0].splitlines()[1:]]
+        code = [ln for ln in code if ln.startswith(".LBB") or ln and not ln.startswith(".")]
+        mfma = [ln.startswith("v_mfma") for ln in code]
+        if not one_wave.search(kernel) or not any(mfma):
+            continue
+        if any(meta.get(kernel, {}).get(k) != "0" for k in (".vgpr_spill_count", ".sgpr_spill_count",
+                                                            ".private_segment_fixed_size")):
+            fail(kernel, "a tile kernel spills, or its resources are not listed")
+        acc = [not m and re.search(r"\ba(?:\d|\[)", ln) is not None for m, ln in zip(mfma, code)]
+        before = {}  # position -> positions that may run just before it
+        labels = {ln[:-1]: i for i, ln in enumerate(code) if ln.endswith(":")}
+        for i, ln in enumerate(code):
+            op, _, target = ln.partition(" ")
+            if target in labels:
+                before.setdefault(labels[target], []).append(i)
+            if op not in ("s_branch", "s_endpgm") and i + 1 < len(code):
+                before.setdefault(i + 1, []).append(i)
+
+        def within(start, states, hit):
+            """A position of `hit` reached backwards from start over less than `states` wait states."""
+            todo, seen = [(p, states) for p in before.get(start, [])], {}
+            while todo:
+                i, left = todo.pop()
+                if hit[i]:
+                    return True
+                left -= 0 if code[i].endswith(":") else int(code[i].split()[1]) + 1 if code[i].startswith("s_nop") else 1
+                if left > 0 and seen.get(i, 0) < left:
+                    seen[i] = left
+                    todo += [(p, left) for p in before.get(i, [])]
+            return False
+        if any(within(i, 20, mfma) for i in range(len(code)) if acc[i]) or \
+                any(within(i, 4, acc) for i in range(len(code)) if mfma[i]):
+            fail(kernel, "an accumulator is touched beside the MFMAs of a tile kernel")
+        count += 1
+    if count == 0:
+        raise RuntimeError(f"{name}: no tile kernel found to check")
+    return count
 
 
 def build(verbose: bool = False) -> str:
@@ -51,27 +112,24 @@ def build(verbose: bool = False) -> str:
         msgs = [ln for ln in (res.stdout + res.stderr).splitlines() if "packed-fp32-ops" not in ln]
         if res.returncode != 0:
             raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
-        remarks = [ln for ln in msgs if "kernel-resource-usage" in ln]
-        msgs = [ln for ln in msgs if "kernel-resource-usage" not in ln and not re.match(r"^\s*\d*\s*\||^\s*\^", ln)]
         if verbose and msgs:
             print("\n".join(msgs), flush=True)
-        return remarks
 
     def compile_one(name, obj):
         extra = ["-mllvm", "-amdgpu-mfma-vgpr-form"] if name in VGPR_FORM else []
-        kernel = ""
-        for ln in run([hipcc()] + flags + extra + ["-Rpass-analysis=kernel-resource-usage", "-c", "-o", obj,
-                                                   os.path.join(CSRC, name)]):
-            if "Function Name:" in ln:
-                kernel = ln
-            # tiles whose MFMAs are instructions of their own: no spill may touch their accumulators
-            elif "Shape4" in kernel and "Spill" in ln and not re.search(r"Spill: 0\b", ln):
-                raise RuntimeError(f"{name}: a four-wave tile kernel spills: {kernel} {ln}")
+        cmd = [hipcc()] + flags + extra
+        if obj.endswith(".s"):
+            run(cmd + ["--cuda-device-only", "-S", "-o", obj, os.path.join(CSRC, name)])
+            with open(obj) as f:
+                check_tile_kernels(name, f.read())
+        else:
+            run(cmd + ["-c", "-o", obj, os.path.join(CSRC, name)])
 
     with tempfile.TemporaryDirectory() as tmp:
         objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
-        with ThreadPoolExecutor(max_workers=4) as pool:
-            list(pool.map(compile_one, SOURCES, objs))
+        with ThreadPoolExecutor(max_workers=6) as pool:
+            listings = [os.path.join(tmp, s + ".s") for s in sorted(CHECKED)]
+            list(pool.map(compile_one, SOURCES + sorted(CHECKED), objs + listings))
         run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", out_tmp] + objs)
     os.replace(out_tmp, LIB_PATH)
     return LIB_PATH
