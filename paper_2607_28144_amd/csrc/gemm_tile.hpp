@@ -4,23 +4,22 @@
 // tile (mma4, store4) for most shapes; eight (tile_body) for tiles of 288 rows
 // and for some of 256.
 //
-// Eight waves.  Workgroup = 8 waves (two per SIMD) = one BM x BN output tile, BN = 16 NB
-// WN; the waves form an (8 / WN) x WN grid, each owning (BM / (8 / WN)) rows
-// x 16 NB channels on v_mfma_f32_16x16x32_bf16.  The product is formed
-// transposed, C^T = W A^T, so that a lane's accumulator holds four
-// consecutive output channels of one row (what the epilogues want).  K
-// advances in steps of 64: both operand tiles go HBM -> LDS with
-// global_load_lds_dwordx4 (no register staging) into a double-buffered LDS
-// ring; rows are 128 bytes, 16-byte chunk c of row r stored at chunk
-// c ^ ((r >> 1) & 7), which makes the fragment reads (16 rows, one chunk)
-// bank-conflict free.  Tiles are dealt XCD-aware: each XCD takes a
-// contiguous range of tiles, numbered in groups of four row blocks swept
-// across the channel blocks, so that the tiles resident on an XCD share
+// Eight waves (dense rows only).  Workgroup = 8 waves (two per SIMD) = one BM
+// x 256 output tile; the waves form a 2 x 4 grid, each owning BM / 2 rows x 64
+// channels on v_mfma_f32_16x16x32_bf16.  The product is formed transposed, C^T
+// = W A^T, so that a lane's accumulator holds four consecutive output channels
+// of one row (what the epilogues want).  K advances in steps of 64: both
+// operand tiles go HBM -> LDS with global_load_lds_dwordx4 (no register
+// staging) into a double-buffered LDS ring; rows are 128 bytes, 16-byte chunk c
+// of row r stored at chunk c ^ ((r >> 1) & 7), which makes the fragment reads
+// (16 rows, one chunk) bank-conflict free.  Tiles are dealt XCD-aware: each XCD
+// takes a contiguous range of tiles, numbered in groups of four row blocks
+// swept across the channel blocks, so that the tiles resident on an XCD share
 // their operand blocks through its L2.
 //
-// The A source is a policy: for each of this lane's copy rows it gives the
-// address of the 16 bytes to copy at K step kt (a dense row, or a tap of a
-// convolution patch, or a page of zeros for padding).
+// Four waves: see below.  Their operand rows are a policy that gives, for each
+// of a lane's copy rows, the address of the 16 bytes to copy at K step kt: a
+// dense row, or a tap of a convolution patch, or a page of zeros for padding.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -50,13 +49,11 @@ enum Epi : int32_t {
 
 // Output side of a tile launch.
 struct Out {
-    const uint16_t *w;    // [N, K] bf16, K contiguous
     const uint16_t *bias; // [N] bf16 or null
     const float *gate;    // [N] f32 or null (kGatedRes)
     void *out;            // bf16 or f32 [M, N], row stride ldo
     int64_t ldo;
-    int32_t M, N, K;
-    int32_t splits;       // kPartial: K split into this many contiguous ranges, one per launch slice
+    int32_t M, N;
 };
 
 #pragma clang diagnostic push
@@ -123,13 +120,15 @@ __device__ __forceinline__ void tile_of(int bid, int tiles_n, int n_tiles, int &
     tn = in_group / gm;
 }
 
-// One BM x BN output tile of eight waves.
-template <int BM, int WN, int EPI, class ASrc, int NB = 4>
-__device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int tiles_n, int n_tiles, char *smem)
+// One BM x BN output tile of eight waves: rows a [M, K] (row stride lda), w [N, K].
+constexpr int kBN = 256;
+template <int BM, int EPI>
+__device__ __forceinline__ void tile_body(const uint16_t *a, int64_t lda, const uint16_t *w, int K, const Out &o,
+                                          int tiles_n, int n_tiles, char *smem)
 {
-    constexpr int BN = 16 * NB * WN;     // NB 16-channel MFMA blocks per wave across
-    constexpr int WGM = kWaves / WN;     // waves along M
-    constexpr int WM = BM / WGM;         // rows per wave
+    constexpr int WN = 4, NB = 4;        // waves across, 16-channel MFMA blocks of each
+    constexpr int BN = kBN;
+    constexpr int WM = BM / 2;           // rows per wave
     constexpr int MB = WM / 16;          // 16-row MFMA blocks per wave
     constexpr int A_BYTES = BM * kRowBytes;
     constexpr int W_BYTES = BN * kRowBytes;
@@ -138,7 +137,7 @@ __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int ti
     constexpr int W_INSTR = W_BYTES / 1024;
     constexpr int A_PER = (A_INSTR + kWaves - 1) / kWaves;
     constexpr int W_PER = W_INSTR / kWaves;
-    static_assert(WM % 16 == 0 && W_INSTR % kWaves == 0, "tile shape");
+    static_assert(WM % 16 == 0 && BN == 16 * NB * WN && W_INSTR % kWaves == 0, "tile shape");
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -153,19 +152,19 @@ __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int ti
     // lane l fills LDS chunk l % 8 of row 8j + l / 8, which holds global
     // chunk swz(row, l % 8).  Rows past the end re-read the last row (never
     // stored).
-    typename ASrc::Row arow[A_PER];
+    const uint16_t *asrc[A_PER];
 #pragma unroll
     for (int i = 0; i < A_PER; ++i) {
         const int j = min(wave + i * kWaves, A_INSTR - 1);
         const int r = j * 8 + (lane >> 3);
-        arow[i] = asrc.row(min(m0 + r, o.M - 1), swz(r, lane & 7));
+        asrc[i] = a + (int64_t)min(m0 + r, o.M - 1) * lda + swz(r, lane & 7) * 8;
     }
     const uint16_t *wsrc[W_PER];
 #pragma unroll
     for (int i = 0; i < W_PER; ++i) {
         const int r = (wave + i * kWaves) * 8 + (lane >> 3);
         const int gr = min(n0 + r, o.N - 1);
-        wsrc[i] = o.w + (int64_t)gr * o.K + swz(r, lane & 7) * 8;
+        wsrc[i] = w + (int64_t)gr * K + swz(r, lane & 7) * 8;
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char *)smem;
     auto issue = [&](int kt, int st) {
@@ -173,7 +172,7 @@ __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int ti
 #pragma unroll
         for (int i = 0; i < A_PER; ++i) {
             const int j = wave + i * kWaves;
-            if (j < A_INSTR) lds_copy16(asrc.src(arow[i], kt), sa + j * 1024);
+            if (j < A_INSTR) lds_copy16(asrc[i] + kt * kBK, sa + j * 1024);
         }
 #pragma unroll
         for (int i = 0; i < W_PER; ++i) lds_copy16(wsrc[i] + kt * kBK, sw + (wave + i * kWaves) * 1024);
@@ -185,7 +184,7 @@ __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int ti
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const int nk = o.K / kBK;
+    const int nk = K / kBK;
     issue(0, 0);
     for (int kt = 0; kt < nk; ++kt) {
         const int st = kt & 1;
@@ -357,13 +356,13 @@ __device__ __forceinline__ void tile_body(const ASrc &asrc, const Out &o, int ti
     }
 }
 
-// LDS bytes of a BM x (16 NB WN) tile: its double-buffered ring, or the
-// bf16 output staging if that is larger.
-template <int BM, int WN, int NB = 4>
+// LDS bytes of a BM x 256 tile of eight waves: its double-buffered ring, or the
+// output staging if that is larger.
+template <int BM>
 constexpr int lds_bytes()
 {
-    constexpr int ring = 2 * (BM + 16 * NB * WN) * kRowBytes;
-    constexpr int staging = BM * 16 * NB * WN * 2;  // bf16 tile, or half of it in fp32
+    constexpr int ring = 2 * (BM + kBN) * kRowBytes;
+    constexpr int staging = BM * kBN * 2;  // bf16 tile, or half of it in fp32
     return ring > staging ? ring : staging;
 }
 
@@ -802,7 +801,6 @@ __device__ __forceinline__ void store4(const Out &o, int m0, int n0, int sp, cha
     }
 }
 
-// XCD-aware tile count helpers for the launchers.
 inline int tiles_along(int n, int b)
 {
     return (n + b - 1) / b;

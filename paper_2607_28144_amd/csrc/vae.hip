@@ -184,8 +184,7 @@ void conv3d_kernel(ConvArgs a, int tiles_n, int n_tiles, int splits)
     const ConvW<WIDE> ws{{static_cast<const uint16_t *>(a.w), (int64_t)kTaps * a.Cin, a.Cout, n0}, a.Cin};
     f32x4 acc[S::NB][S::MB];
     tile::mma4<S>(as, ws, k0, k1, smem, acc);
-    const tile::Out o{nullptr, static_cast<const uint16_t *>(a.bias), nullptr, PART ? a.ws : a.out, a.Cout, M, a.Cout,
-                      27 * a.Cin, splits};
+    const tile::Out o{static_cast<const uint16_t *>(a.bias), nullptr, PART ? a.ws : a.out, a.Cout, M, a.Cout};
     tile::store4<S, EPI>(o, m0, n0, sp, smem, acc);
 }
 
