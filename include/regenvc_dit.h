@@ -58,9 +58,11 @@ extern "C" {
            (row stride ldo), read and rewritten, for GATED_RESIDUAL
    M, N, K >= 0; K a multiple of 64; N a multiple of 16; lda, ldo multiples
    of 8 and >= K, N; pointers 16-byte aligned (bias, gate too) -- else
-   REGENVC_ERR_UNSUPPORTED.  out must not overlap a, w, bias or gate.  Rows
-   go in tiles of 256 or 288 (whichever fills the compute units in fewer
-   rounds) by 256 channels. */
+   REGENVC_ERR_UNSUPPORTED.  out must not overlap a, w, bias or gate.  The
+   output tile, 64 x 128 to 288 x 256, is chosen by size
+   (regenvc_linear_plan_query).  A call is deterministic, and without a split
+   of K (below) an output element is the same sum in the same order whatever
+   the tile: a row comes out alike in calls of any number of rows. */
 regenvc_status regenvc_linear_fwd(const void *a, int64_t lda, const void *w, const void *bias,
                                   const float *gate, void *out, int64_t ldo, int32_t M, int32_t N,
                                   int32_t K, int32_t epilogue, void *stream);
@@ -70,7 +72,10 @@ regenvc_status regenvc_linear_fwd(const void *a, int64_t lda, const void *w, con
    is cut into ranges whose f32 partial sums go to the workspace and a second
    kernel adds them, in order, with the epilogue.  A workspace smaller than
    regenvc_linear_workspace gives fewer ranges; without one the call is
-   regenvc_linear_fwd.  Neither call allocates. */
+   regenvc_linear_fwd.  The number of ranges, and with it the rounding of a row,
+   depends on M, N, K, the epilogue, the compute units and the workspace: a
+   shard of rows and the whole may differ by fp32 summation order.  Neither
+   call allocates. */
 regenvc_status regenvc_linear_fwd_ws(const void *a, int64_t lda, const void *w, const void *bias, const float *gate,
                                      void *out, int64_t ldo, int32_t M, int32_t N, int32_t K, int32_t epilogue,
                                      void *workspace, int64_t workspace_bytes, void *stream);

@@ -63,8 +63,8 @@ regenvc_status regenvc_vae_split(int32_t H, int32_t W, int32_t ty, int32_t tx, i
           region height or columns >= region width are unspecified
      workspace: NULL, or caller-owned DEVICE memory of workspace_bytes
           (256-byte aligned, not overlapping any other argument) for the
-          split-K form: when the output tiles would leave most compute units
-          idle (one GPU's single tile), K is cut into ranges whose f32
+          split-K form: where the output has too few tiles for the chip (one
+          GPU's single tile), K is cut into ranges whose f32
           partial sums go to the workspace and a second kernel adds them,
           the bias and the activation.  Up to
           regenvc_vae_conv3d_workspace bytes are used; less gives fewer

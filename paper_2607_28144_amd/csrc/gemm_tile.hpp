@@ -640,8 +640,8 @@ __device__ __forceinline__ void mma4(const ASrc &as, const WSrc &ws, int k0, int
 // An accumulator's value for the epilogue, by explicit moves where mfma_into
 // is an instruction of its own: no other code then touches those registers,
 // so that none can be placed (a copy, a spill) between the last MFMAs and the
-// wait states that end mma4.  build.py refuses a build in which one of these
-// kernels spills.
+// wait states that end mma4.  build.py reads the assembly of these kernels and
+// refuses one that spills, or touches an accumulator near its MFMAs.
 template <class S>
 __device__ __forceinline__ f32x4 acc_value(f32x4 &a)
 {

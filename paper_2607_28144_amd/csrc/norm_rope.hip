@@ -17,7 +17,12 @@
 // token.  10920 tokens of 12 heads x 128 (134 MB): 34.9 -> 25.0 us (5.3 TB/s;
 // a large copy reaches 5.1), 1560 tokens 8.9 -> 6.2 us, 300 tokens 6.2 -> 4.5
 // us; with the angles formed per chunk and 64-bit divisions per token the
-// vector unit was what bound it.
+// vector unit was what bound it.  What a wave holds costs it neighbours: 188
+// registers at 1536 channels are two waves per SIMD, so the window's 3640 waves
+// run as 1.8 rounds of 2048; from 4097 to 8192 channels (256 registers, no next
+// token held) one wave per SIMD still takes less time than two of the former
+// kernel did (10920 tokens of 40 heads x 128 138 -> 102 us, of 64 heads 215 ->
+// 154 us).
 #include "attn_kernels.hpp"
 
 #include <math.h>
@@ -28,6 +33,8 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // eight bf16, the first of a pair in the low half
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
+// Waves launched per compute unit, at most: where registers allow fewer at a
+// time, the rest follow.
 constexpr int kWavesPerCu = 16;
 constexpr float kInv2Pi = 0.15915494309189535f;
 
@@ -58,7 +65,7 @@ __global__ __launch_bounds__(64) void qk_norm_rope_kernel(NormRopeArgs a)
     const float inv_c = 1.0f / (float)C;
     constexpr int P = D / 2, ph = D / 6, pf = P - 2 * ph;  // pairs of a head, of its row and column axes, of its frame axis
 
-    // this lane's place in its heads, and the frequencies (turns per position) and axes of its four pairs
+    // this lane's place in its heads, and the frequencies (radians per position) and axes of its four pairs
     const int d0 = (lane * 8) % D, h0 = (lane * 8) / D;
     constexpr int kHeadStep = 512 / D;
     float freq[4];
@@ -166,8 +173,8 @@ __global__ __launch_bounds__(64) void qk_norm_rope_kernel(NormRopeArgs a)
 template <int D>
 hipError_t launch_d(const NormRopeArgs &a, hipStream_t stream)
 {
-    // up to 16 waves per compute unit, each with its share of the tokens; a
-    // wave of more than four chunks per lane has no registers for a next token
+    // each wave has its share of the tokens; one of more than four chunks per
+    // lane has no registers for a next token
     const int64_t tokens = (int64_t)a.B * a.S, slots = (int64_t)device_cu_count() * kWavesPerCu;
     const int nch = (a.H * D + 511) / 512;
     const int64_t per = nch <= 4 ? (tokens + slots - 1) / slots : 1;

@@ -9,9 +9,12 @@
 namespace regenvc {
 
 // One tile shape: a workgroup's fixed time (launch, first copies, epilogue;
-// unsplit and split) and its time per 64-deep K step, in us, measured on launches of at most one
-// round, and the factor by which full rounds are slower (the clock that the
-// power limit leaves, shared LDS and memory).
+// unsplit and split) and its time per 64-deep K step, in us, and a factor on
+// rounds of n_cu workgroups (the clock that the power limit leaves, shared LDS
+// and memory).  Fitted, all together, to the times of whole launches.  Rounds
+// are counted as if each compute unit ran one workgroup at a time; the small
+// tiles, two or three of which it runs side by side, have the gain of that in
+// their factor, which is then below one.
 struct TileCost {
     int32_t tile, bm, bn, waves;
     double fixed, fixed_split, step, load;

@@ -282,13 +282,15 @@ hipError_t launch_conv(const ConvArgs &a, int splits, hipStream_t stream)
 
 }  // namespace
 
-// The tile and K split of a convolution, by plan_tiles; the constants are
-// fitted to 23 shapes of 768 to 64736 pixels and 128 to 384 channels.  64736
-// pixels x 384 channels: 430 -> 380 to 393 us a convolution (256 x 192, 506
-// tiles: two rounds), one tile of the split plane (8092 pixels) 72.7 -> 66.9 us
-// (128 x 192 in two ranges; 256 x 192 in four 69.1, its partials twice the
-// bytes), 3468 pixels x 384 channels 37.8 us (128 x 128 in three).  A step costs
-// a fifth more than a linear layer's: its pixel addresses are selected in
+// The tile and K split of a convolution, by plan_tiles with constants fitted to
+// timed launches.  Over 110 shapes of 320 to 174720 pixels and 64 to 512
+// channels, each timed on every tile and split, the choice is on average 1.2 %
+// slower than the best, at most 18 % (43680 pixels x 256 -> 128 channels, 97 us
+// on 192 x 192, 82 on 128 x 128).  64736 pixels x 384 channels: 416-420 ->
+// 362-370 us a convolution (256 x 192, 506 tiles: two rounds); one tile of the
+// split plane (8092 pixels) 68.0 + 9.2 -> 68.7 + 6.4 us with the second kernel
+// (128 x 192 in two ranges, where four wrote twice the partial sums).  A step
+// costs a fifth more than a linear layer's: its pixel addresses are selected in
 // vector registers.
 TilePlan conv_plan(int64_t M, int N, int Cin, int n_cu, int64_t ws_bytes)
 {

@@ -176,6 +176,30 @@ def test_linear_wide_row_stride():
     assert torch.equal(got, kern().linear_fwd(da.contiguous(), dw))
 
 
+@pytest.mark.parametrize("N,rows", [(1536, (1, 1365, 2731, 5461, 8193)),   # seven tiles between them and the epilogues
+                                    (1552, (1, 1365, 2731, 5461, 8193))])  # 160 x 256 and ragged channels
+@pytest.mark.parametrize("epi", [0, 1, 2])
+def test_rows_come_out_alike_without_a_split(N, rows, epi):
+    """Without a workspace a row is bitwise the same in a call of any number of
+    rows, on whatever tile."""
+    import ctypes
+    from paper_2607_28144_amd import _lib
+    M, K, lib = 10921, 512, _lib.load()
+    r = torch.Generator(device="cuda").manual_seed(N)
+    rand = lambda *n: torch.randn(*n, generator=r, device="cuda")  # noqa: E731
+    a, w, b, gate, x0 = rand(M, K).bfloat16(), (rand(N, K) * 0.02).bfloat16(), rand(N).bfloat16(), rand(N), rand(M, N)
+
+    def call(m):
+        out = x0[:m].clone() if epi == 2 else torch.empty(m, N, dtype=torch.bfloat16, device="cuda")
+        _lib.check(lib.regenvc_linear_fwd(a.data_ptr(), K, w.data_ptr(), b.data_ptr(), gate.data_ptr() if epi == 2 else None,
+                                          out.data_ptr(), N, m, N, K, epi,
+                                          ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)), "regenvc_linear_fwd")
+        return out
+    whole = call(M)
+    for m in rows:
+        assert torch.equal(call(m), whole[:m]), m
+
+
 def test_linear_split_workspace_sizes():
     """The split-K form under a workspace that is missing, too small for any
     split, enough for some and enough for all ranges."""
