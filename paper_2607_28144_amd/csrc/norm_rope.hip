@@ -62,7 +62,6 @@ __global__ __launch_bounds__(64) void qk_norm_rope_kernel(NormRopeArgs a)
     const int lane = threadIdx.x & 63;
     const int64_t tokens = (int64_t)a.B * a.S;
     const int C = a.H * D, nchunk = C / 8;
-    const float inv_c = 1.0f / (float)C;
     constexpr int P = D / 2, ph = D / 6, pf = P - 2 * ph;  // pairs of a head, of its row and column axes, of its frame axis
 
     // this lane's place in its heads, and the frequencies (radians per position) and axes of its four pairs
@@ -124,8 +123,13 @@ __global__ __launch_bounds__(64) void qk_norm_rope_kernel(NormRopeArgs a)
         if constexpr (KEEP) {
             if (token + gridDim.x < tokens) load(token + gridDim.x, qn, kn);
         }
-        const float rq = 1.0f / sqrtf(wave_sum(sq) * inv_c + a.eps);
-        const float rk = 1.0f / sqrtf(wave_sum(sk) * inv_c + a.eps);
+        // 1/sqrt of q's mean square in the lower lanes and k's in the upper: one
+        // sequence for both.  The mean by division: a product with 1 / C is
+        // rounded twice.
+        const float tq = wave_sum(sq), tk = wave_sum(sk);
+        const int r = __float_as_int(1.0f / sqrtf((lane < 32 ? tq : tk) / (float)C + a.eps));
+        const float rq = __int_as_float(__builtin_amdgcn_readlane(r, 0));
+        const float rk = __int_as_float(__builtin_amdgcn_readlane(r, 32));
 
         // this token's grid position (token0 + S < 2^32) and its sines and cosines
         int64_t b, t;

@@ -123,3 +123,22 @@ def test_head_major_input_layout():
 ])
 def test_chunks_and_tokens_per_wave(B, S, H, D, grid):
     run(f"B={B} S={S} H={H} D={D}", 90 + H + D, B, S, H, D, grid)
+
+
+def test_mean_square_is_rounded_once():
+    """A token of 41 heads x 64 at position 0 (no rotation), whose 2624 squares
+    sum to 2624 exactly: mean square and norm are 1, and x w is the output.
+    130/128 times 1.25 lies halfway between two bf16 values and goes to the
+    even, lower one.  (2624 times 1/2624, each rounded to float32, is one ulp
+    below 1, which takes that product to the upper value.)"""
+    H, D = 41, 64
+    x, w = np.ones(H * D, np.float32), np.ones(H * D, np.float32)
+    tie = np.concatenate([np.arange(8), 512 + np.arange(8)])  # channels of one lane: its part of the sum is whole
+    x[tie], w[tie] = 130 / 128, 1.25
+    x[1024:1028] = np.array([236, 36, 12, 12]) / 128
+    assert float((x.astype(np.float64) ** 2).sum()) == H * D
+    qk, wb = dev(synth.f32_to_bf16_bits(x).reshape(1, 1, H, D)), dev(synth.f32_to_bf16_bits(w))
+    ref = dev(synth.f32_to_bf16_bits(x * w).reshape(1, 1, H, D))
+    assert float(ref.flatten()[0]) == 162 / 128
+    q, k = api().qk_norm_rope(qk, qk.clone(), wb, wb, (1, 1, 1), eps=0.0)
+    assert torch.equal(q, ref) and torch.equal(k, ref)
