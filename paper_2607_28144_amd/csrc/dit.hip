@@ -350,7 +350,7 @@ hipError_t launch_linear4(const LinearArgs &a, int splits, hipStream_t stream)
 // choice is on average 1.0 % slower than the best of them.  Measured, against
 // 256 x 256 or 288 x 256 by eight waves alone:
 // 1365 x 1536 x 8960 203 -> 47 us (192 x 192 in four ranges),
-// 1560 x 4608 x 1536 39.7 -> 23.5 us (128 x 128), 4096 x 1536 x 8960 205 -> 99 us
+// 1560 x 4608 x 1536 39.7 -> 23.5 us (128 x 128), 4096 x 1536 x 8960 205 -> 94 us
 // (128 x 192), 10920 x 8960 x 1536 with GELU 286 -> 254 us (256 x 256 by four
 // waves); 10920 x 4608 and 10920 x 1536 stay with 288 x 256 by eight waves
 // (125 and 43.7 us: 228 tiles of 288 rows are one round where 43 row blocks of
